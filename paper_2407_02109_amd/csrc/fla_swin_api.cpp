@@ -22,7 +22,8 @@ constexpr int64_t kMaxGroups = (int64_t(1) << 23) - 1;   // grid.x * 512 threads
 // Windows of a grid list: the canvas has `origin` virtual tokens in front of each axis;
 // window i of an axis covers canvas [i*window, (i+1)*window) = grid [i*window - origin, ...).
 struct Geometry {
-    int origin, nqb, nbb, n_windows;   // nbb: bf16 backward blocks of kBwdBlock tokens
+    int origin, nqb, nbb, n_windows;   // nbb: backward blocks of kBwdBlock tokens
+    int n_max;                   // tokens of the largest window
     int64_t L;                   // tokens per batch entry
     int64_t n_groups;
     fla::GridDesc grid[fla::kMaxGrids];
@@ -68,6 +69,7 @@ bool geometry(int B, int heads, int n, const int* hw, int window, int shift, Geo
     }
     g->n_windows = (int)wins;
     g->L = L;
+    g->n_max = (int)nmax;
     g->nqb = (int)((nmax + fla::kQueryBlock - 1) / fla::kQueryBlock);
     g->nbb = (int)((nmax + fla::kBwdBlock - 1) / fla::kBwdBlock);
     g->n_groups = int64_t(B) * heads * wins * g->nqb;
@@ -190,6 +192,7 @@ fla::SwinArgs make_args(const Problem& pr, const void* q, const void* k, const v
     a.shift = shift;
     a.origin = geo.origin;
     a.nqb = geo.nqb;
+    a.n_max = geo.n_max;
     a.pad_mode = pad_mode;
     a.L = pr.L;
     a.tok_stride = pr.tok;

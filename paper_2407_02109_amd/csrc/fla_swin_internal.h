@@ -34,7 +34,8 @@ struct FastDiv {
 constexpr int kHeadDim = 64;    // head_dim of every kernel (the training, RoPE and backward paths)
 // head_dim values of the plain forward kernels (bf16 and fp32): 64, and the instances 32 and 128
 __host__ __device__ constexpr bool fwd_head_dim_ok(int d) { return d == 32 || d == 64 || d == 128; }
-constexpr int kQueryBlock = 256; // queries of one window handled by one workgroup
+constexpr int kQueryBlock = 256; // queries of one window handled by one bf16 forward workgroup
+constexpr int kBwdBlock = 128;   // tokens of one backward block
 
 constexpr int kMaxGrids = 8;    // token grids of one multi-scale sequence
 
@@ -59,6 +60,7 @@ struct SwinArgs {
     int window, shift;
     int origin;                 // (window - shift) % window: virtual tokens in front of each axis
     int nqb;                    // query blocks per window: ceil(max window size / kQueryBlock)
+    int n_max;                  // tokens of the largest window
     int pad_mode;               // 0 = mask virtual keys, 1 = pad token at row L
     int64_t L;                  // tokens per batch entry, all grids (the pad token's row)
     int64_t tok_stride;         // elements between consecutive tokens: heads * head_dim
@@ -107,7 +109,6 @@ __device__ __forceinline__ unsigned xcd_rotate(unsigned id, unsigned s) {
 hipError_t launch_swin_fwd_bf16(const SwinArgs& a, hipStream_t stream);
 hipError_t launch_swin_fwd_f32(const SwinArgs& a, hipStream_t stream);
 
-constexpr int kBwdBlock = 128;    // tokens of one bf16 backward block (and of one streamed chunk)
 constexpr int kPadPartial = 2 * kHeadDim;   // floats per pad-gradient partial: dk then dv
 
 // Backward pass: the forward's geometry plus the gradient tensors.  Inputs q, k, v (in f),

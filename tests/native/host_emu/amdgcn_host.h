@@ -4,7 +4,7 @@
 //
 // Lane-local builtins are plain functions.  The wave-level ones (the 32x32x16 bf16 matrix
 // product, the half-wave swap, the ballot) exchange their operands through a per-wave slot
-// area between two barriers over the wave's 64 lanes, which the launch emulation provides:
+// area around a barrier over the wave's 64 lanes, which the launch emulation provides:
 // every lane of a wave must reach them together, as on the hardware, or the run deadlocks
 // (the tests bound it with a time limit).  Buffer resources keep the base and the byte
 // range; a load outside the range returns zeros and a store outside it is dropped, dword by
@@ -27,7 +27,9 @@ typedef unsigned emu_u32x2 __attribute__((ext_vector_type(2)));
 // provided by the launch emulation (emu.cpp)
 unsigned emu_lane_id();
 void emu_wave_barrier();
-unsigned char* emu_wave_slots();   // this wave's 64 slots of 64 bytes
+// this wave's 64 slots of 64 bytes, two areas in turn: an exchange is write, barrier, read, and the
+// next one writes the other area, so a lane that has read may go on while others still read
+unsigned char* emu_wave_slots();
 
 inline unsigned __float_as_uint(float x) {
     unsigned u;
@@ -106,7 +108,36 @@ inline emu_floatx16 __builtin_amdgcn_mfma_f32_32x32x16_bf16(emu_bf16x8 a, emu_bf
             acc += (float)s[i + 32 * (k >> 3)].a[k & 7] * (float)s[n + 32 * (k >> 3)].b[k & 7];
         d[r] += acc;
     }
+    return d;
+}
+
+// D = A B + C, A 32 x 2, B 2 x 32, fp32.  Lane l supplies element l / 32 of row l % 32 of A and of
+// column l % 32 of B; D as above.
+inline emu_floatx16 __builtin_amdgcn_mfma_f32_32x32x2f32(float a, float b, emu_floatx16 c, int, int, int) {
+    float* s = reinterpret_cast<float*>(emu_wave_slots());
+    const unsigned l = emu_lane_id();
+    s[l] = a;
+    s[64 + l] = b;
     emu_wave_barrier();
+    const unsigned n = l & 31, h = l >> 5;
+    emu_floatx16 d = c;
+    for (int r = 0; r < 16; ++r) {
+        const unsigned i = 8 * (r >> 2) + 4 * h + (r & 3);
+        d[r] = std::fma(s[i + 32], s[64 + n + 32], std::fma(s[i], s[64 + n], d[r]));
+    }
+    return d;
+}
+
+// 16 outer products of 4 x 1 and 1 x 4, D = A B + C: lane l supplies row l % 4 of A and column l % 4
+// of B of block l / 4 and receives that column of D, row r in element r.
+typedef float emu_floatx4 __attribute__((ext_vector_type(4)));
+inline emu_floatx4 __builtin_amdgcn_mfma_f32_4x4x1f32(float a, float b, emu_floatx4 c, int, int, int) {
+    float* s = reinterpret_cast<float*>(emu_wave_slots());
+    const unsigned l = emu_lane_id();
+    s[l] = a;
+    emu_wave_barrier();
+    emu_floatx4 d = c;
+    for (int r = 0; r < 4; ++r) d[r] = std::fma(s[(l & ~3u) + r], b, d[r]);
     return d;
 }
 
@@ -126,7 +157,6 @@ inline emu_u32x2 __builtin_amdgcn_permlane32_swap(unsigned x, unsigned y, bool, 
         r[0] = s[2 * (l - 32) + 1];
         r[1] = y;
     }
-    emu_wave_barrier();
     return r;
 }
 
@@ -138,7 +168,6 @@ inline unsigned long long __builtin_amdgcn_ballot_w64(bool p) {
     unsigned long long m = 0;
     for (int i = 0; i < 64; ++i)
         if (s[i]) m |= 1ull << i;
-    emu_wave_barrier();
     return m;
 }
 
@@ -159,7 +188,6 @@ inline emu_shortx4 __builtin_amdgcn_ds_read_tr16_b64_v4i16(__attribute__((addres
     const unsigned g = l & ~15u, i = l & 15u;
     emu_shortx4 r;
     for (int row = 0; row < 4; ++row) r[row] = s[g + 4 * row + i / 4][i % 4];
-    emu_wave_barrier();
     return r;
 }
 
@@ -178,13 +206,13 @@ inline void __builtin_amdgcn_raw_ptr_buffer_load_lds(__amdgpu_buffer_rsrc_t r, _
     }
 }
 inline void __builtin_amdgcn_s_waitcnt(int) { emu_wave_barrier(); }
+inline void __builtin_amdgcn_sched_barrier(int) {}   // orders the compiler's schedule only
 
 inline int __builtin_amdgcn_readfirstlane(int x) {
     int* s = reinterpret_cast<int*>(emu_wave_slots());
     s[emu_lane_id()] = x;
     emu_wave_barrier();
     const int r = s[0];
-    emu_wave_barrier();
     return r;
 }
 
@@ -196,6 +224,5 @@ inline T __shfl_xor(T x, int mask, int = 64) {
     s[l] = x;
     emu_wave_barrier();
     const T r = s[(l ^ (unsigned)mask) & 63u];
-    emu_wave_barrier();
     return r;
 }

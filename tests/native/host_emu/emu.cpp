@@ -12,13 +12,14 @@ thread_local emu_index threadIdx, blockIdx;
 static std::barrier<>* g_block_barrier = nullptr;
 void __syncthreads() { g_block_barrier->arrive_and_wait(); }
 
-// waves of 64 work items: a barrier over each wave's lanes and 4 KB of exchange slots per wave
+// waves of 64 work items: a barrier over each wave's lanes and two areas of 4 KB of exchange slots per wave
 constexpr unsigned kEmuMaxWaves = 16;   // workgroups of up to 1024 work items
 static std::vector<std::unique_ptr<std::barrier<>>> g_wave_barriers;
-alignas(64) static unsigned char g_wave_slots[kEmuMaxWaves][4096];
+alignas(64) static unsigned char g_wave_slots[kEmuMaxWaves][2][4096];
+static thread_local unsigned g_exchange;   // exchanges of this lane so far: every lane of a wave counts the same
 unsigned emu_lane_id() { return threadIdx.x & 63u; }
 void emu_wave_barrier() { g_wave_barriers[threadIdx.x >> 6]->arrive_and_wait(); }
-unsigned char* emu_wave_slots() { return g_wave_slots[threadIdx.x >> 6]; }
+unsigned char* emu_wave_slots() { return g_wave_slots[threadIdx.x >> 6][g_exchange++ & 1u]; }
 
 hipError_t hipGetDevice(int* device) {
     *device = 0;

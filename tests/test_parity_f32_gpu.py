@@ -1,0 +1,79 @@
+"""fp32 forward and backward kernels at the edges of their tiles (32 tokens), blocks and chunks
+(64 tokens), against the fp64 oracle.
+
+A window of n tokens is cut into query and key tiles of 32, and each query (key) tile is shared by
+two waves that take its even and odd streamed tiles: n = 1, 31 .. 33 leave the second wave without
+a tile or with one, 63 .. 65 end a block and a chunk, and in KV-token mode n = 64 puts the pad token
+alone into a chunk.  Bounds: 1e-5 absolute for the output (values of order 1) and the log-sum-exp,
+1e-5 of the largest reference gradient: sums of up to 300 products of order 1 in fp32 are off by a
+few 2^-24 times their size (~1e-6 here)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from paper_2407_02109_amd import binding as fb
+from paper_2407_02109_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # B, heads, H, W, window, shift, pad_mode
+    (1, 2, 1, 1, 4, 0, 0),      # one token
+    (1, 1, 1, 31, 33, 0, 1), (1, 1, 1, 32, 33, 0, 1), (2, 3, 3, 11, 12, 0, 0),        # n = 31, 32, 33
+    (1, 1, 7, 9, 9, 0, 0), (1, 2, 8, 8, 9, 0, 1), (1, 2, 8, 8, 8, 0, 0), (1, 1, 5, 13, 13, 0, 1),   # 63, 64, 64, 65
+    (1, 1, 9, 14, 14, 0, 1), (2, 1, 16, 8, 16, 0, 0), (1, 1, 3, 43, 43, 0, 0),        # 126, 128, 129
+    (1, 5, 19, 23, 10, 7, 1),   # shifted, ragged: windows of many sizes, five heads
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c)))
+def test_tile_edges(case):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    B, heads, H, W, k, s, pm = case
+    print("[case] fp32 %s" % (case,), flush=True)
+    wl = synth.Workload("case", B, heads, H, W, 64, k, s, "f32", seed=77, pad_mode=pm)
+    q, kk, v = synth.make_inputs(wl)
+    dout = synth.make_grad(wl)
+    gpu = [t.to("cuda:0") for t in (q, kk, v, dout)]
+    out, lse = fb.swin_attn_fwd_train(*gpu[:3], [(H, W)], k, s, pm)
+    plain = fb.swin_attn(*gpu[:3], H, W, k, s, pm)
+    grads = fb.swin_attn_bwd(*gpu[:3], out, gpu[3], lse, [(H, W)], k, s, pm)
+    torch.cuda.synchronize()
+    assert torch.equal(out, plain)
+    f64 = [synth.to_f64_numpy(t) for t in (q, kk, v, dout)]
+    assert np.abs(synth.to_f64_numpy(out) - O.swin_attention_textbook(*f64[:3], H, W, k, s, pm)).max() <= 1e-5
+    assert np.abs(synth.to_f64_numpy(lse) - O.swin_attention_lse(*f64[:3], H, W, k, s, pm)).max() <= 1e-5
+    for name, got, ref in zip(("dq", "dk", "dv"), grads, O.swin_attention_bwd(*f64, H, W, k, s, pm)):
+        assert np.abs(synth.to_f64_numpy(got) - ref).max() <= 1e-5 * max(1.0, np.abs(ref).max()), name
+
+
+@pytest.mark.parametrize("d", [32, 128])
+@pytest.mark.parametrize("n", [33, 64, 65])
+def test_head_dim_tile_edges(d, n):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print("[case] fp32 head_dim %d, %d tokens" % (d, n), flush=True)
+    wl = synth.Workload("case", 2, 3, 1, n, d, n + 1, 0, "f32", seed=78, pad_mode=1)
+    q, k, v = synth.make_inputs(wl)
+    out = fb.swin_attn(*(t.to("cuda:0") for t in (q, k, v)), 1, n, n + 1, 0, 1)
+    torch.cuda.synchronize()
+    ref = O.swin_attention_textbook(*(synth.to_f64_numpy(t) for t in (q, k, v)), 1, n, n + 1, 0, 1)
+    assert np.abs(synth.to_f64_numpy(out) - ref).max() <= 1e-5
+
+
+def test_minus_infinity_logits_have_no_weight():
+    """Keys whose logits are -inf for every query have weight zero, also when they fill the whole
+    first tile of one of the two waves of a query tile."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print("[case] fp32 logits of -inf", flush=True)
+    g = torch.Generator().manual_seed(5)
+    q, k, v = (torch.randn(1, 64, 1, 64, generator=g) for _ in range(3))
+    q[..., 0] = q[..., 0].abs() + 0.1
+    k[0, :32, 0, 0] = -float("inf")       # the whole first key tile: weight zero for every query
+    ref = torch.nn.functional.scaled_dot_product_attention(
+        *(t.transpose(1, 2).double() for t in (q, k[:, 32:], v[:, 32:]))).transpose(1, 2)
+    out = fb.swin_attn(*(t.to("cuda:0") for t in (q, k, v)), 8, 8, 8, 0, 0)
+    torch.cuda.synchronize()
+    assert (out.cpu().double() - ref).abs().max() <= 1e-5
