@@ -366,7 +366,7 @@ int backward(const void* q, const void* k, const void* v, const void* out, const
     a.ws = static_cast<float*>(ws);
     // bf16: windows of up to 256 tokens (one 256-query block) take the one-window kernel
     const bool window_kernel = elem_bytes == 2 && pr.geo.nqb == 1;
-    a.pad_blocks = elem_bytes != 2 ? pr.geo.nqb : window_kernel ? 1 : pr.geo.nbb;
+    a.pad_blocks = elem_bytes != 2 || window_kernel ? 1 : pr.geo.nbb;
     a.nbb = pr.geo.nbb;
     a.div_2nbb = fla::FastDiv::make(2u * (unsigned)pr.geo.nbb);
     a.n_units = units;

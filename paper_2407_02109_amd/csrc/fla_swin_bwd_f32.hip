@@ -1,270 +1,511 @@
-// Flash Swin attention backward, fp32 storage and arithmetic (vector ALU), and the
-// reduction of the pad token's gradient shared with the bf16 path.
+// Flash Swin attention backward, fp32 storage and arithmetic, gfx950 (CDNA4) matrix cores, and
+// the reduction of the pad token's gradient shared with the bf16 path.
 //
 // The gradients of Eq. 1 inside each window (the paper trains through Flash Swin, App. D),
 // with c = 1/sqrt(d), LSE_i stored by the training forward and D_i = <dO_i, O_i>:
 //   P_ij = w_j exp(c <q_i, k_j> - LSE_i),  dS_ij = P_ij (<dO_i, v_j> - D_i)
 //   dq_i = c sum_j dS_ij k_j,   dk_j = c sum_i dS_ij q_i,   dv_j = sum_i P_ij dO_i
-// Nothing of size n^2 is stored: every kernel recomputes P from q, k and LSE.
+// Nothing of size n^2 is stored: P is recomputed from q, k and LSE.
 //
-// Three kernels over the forward's decomposition (one workgroup per batch entry, window,
-// block of 256 tokens and head):
-//   dq:  one query per thread; keys stream through LDS 64 at a time.  In KV-token mode the
-//        pad token (Sec. 3.4, App. B) is one more key of weight n_pad, and the block also
-//        writes its share of the pad token's own gradient to the workspace.
-//   dv, dk:  one key per thread; queries (q, dO, LSE, D) stream through LDS.
-// The pad reduce kernel then sums the workspace shares in a fixed order into row L of dk
-// and dv, so the result does not depend on scheduling.
+// One launch, two kinds of workgroup (256 threads = 4 waves) per (batch entry, window, block of
+// 64 tokens, head); wave (tt, sh) owns the 32 tokens of tile tt of the block and works on
+// every other 32-row tile of what streams past (tiles sh, sh + 2, ...); the two waves of a tile
+// add their sums at the end:
+//   * key role: the K and V rows of its 32 keys in registers, the window's queries streaming
+//     (Q, dO rows; LSE, D per query):   S = Q K_w^T, dP - D = dO V_w^T - D,
+//     dV_w^T += dO^T P, dK_w^T += Q^T dS;
+//   * query role: the Q and dO rows of its 32 queries in registers, the window's keys streaming:
+//     S^T = K Q_w^T, dP^T - D = V dO_w^T - D, dQ_w^T += K^T dS^T.
+// Products run on v_mfma_f32_32x32x2_f32, laid out as in the fp32 forward: the channel sums take
+// half h = l / 32 of a row's channels per lane, 16 bytes of a streamed row at a time, and the
+// accumulator of S (the streamed rows 8 (r / 4) + 4 h + r % 4 in register r) is, after the
+// elementwise step, the second operand of the product summed over those rows, whose first
+// operand is a 4-byte read of the streamed row.
+//
+// Streamed rows come 64 at a time by buffer loads that write LDS, into one of two buffers: the
+// next chunk's loads are issued when a chunk is published, one barrier per chunk.  The 16-byte
+// pieces of a row are XOR-swizzled by the row.  64 KB of row buffers and up to 256 VGPRs: two
+// workgroups share a compute unit.
+//
+// Bound by the fp32 matrix rate (64 flop per cycle and SIMD): seven products of 32 x 64
+// cycles per pair of 32-token tiles, against five if dS were shared between the roles; sharing
+// it needs the whole window in one workgroup, which leaves most of the chip idle on the small
+// grids that fp32 is used for.
+// Measured, 12 heads, window 16, shift 8: 64x64 tokens 109 us, 128x128 432 us; three kernels of
+// one token per thread on the vector ALU, the streamed rows broadcast from LDS, took 641 and
+// 1708 us.
+//
+// KV-token mode: the pad token (Sec. 3.4, App. B) is one more key of weight n_pad.  The query role
+// adds its dS_p k_p to dQ; the key role of block 0, past which every query of the window streams,
+// sums the pad token's own gradient over them into the workspace, one partial per window.
+// The pad reduce kernel then sums those in a fixed order into row L of dk and dv, so the
+// result does not depend on scheduling.
 #include "fla_swin_device.h"
 
 namespace fla {
 namespace {
 
 constexpr int D = kHeadDim;
-constexpr int THREADS = kQueryBlock;   // one token per thread
-constexpr int CH = 64;                 // tokens per LDS chunk
-constexpr float kLog2e = 1.4426950408889634f;
+constexpr int THREADS = 256;
+constexpr int NW = THREADS / 64;
+constexpr int TL = 32;                 // tokens per tile
+constexpr int TB = 2 * TL;             // tokens per block: two waves per tile
+constexpr int CH = 2 * TL;             // streamed rows per chunk: one tile per sh
+constexpr int ROWP = D / 4;            // 16-byte pieces per row
+constexpr int BUF = CH * D;            // floats of one chunk's rows of one tensor
+constexpr unsigned kGridX = 1u << 22;  // workgroups per row of the launch grid
+// log2(e) in two parts: LSE log2(e) is kept as a pair, so that P carries the rounding of the
+// stored LSE and not that of a product of its size as well
+constexpr float kLog2eHi = 1.44269502f, kLog2eLo = 1.92596303e-8f;
 
+// LDS, floats: two buffers of X rows (Q or K) and Y rows (dO or V); per streamed query of each
+// buffer LSE log2(e) (two parts), -D, and the pad token's P and dS; the pad token's k and v rows,
+// and two half sums per channel of its gradient.  After the last chunk the row buffers hold the
+// exchanged halves of the accumulators (OFF_EXCH) and the finished rows.
+constexpr int OFF_X = 0;
+constexpr int OFF_Y = OFF_X + 2 * BUF;
+constexpr int OFF_LH = OFF_Y + 2 * BUF;
+constexpr int OFF_LL = OFF_LH + 2 * CH;
+constexpr int OFF_ND = OFF_LL + 2 * CH;
+constexpr int OFF_PP = OFF_ND + 2 * CH;
+constexpr int OFF_DSP = OFF_PP + 2 * CH;
+constexpr int OFF_PADKV = OFF_DSP + 2 * CH;
+constexpr int OFF_PADW = OFF_PADKV + 2 * D;
+constexpr int LDS = OFF_PADW + THREADS;
+constexpr int OFF_ROWS = 2 * BUF;      // finished rows: two tensors of TB rows (OFF_Y's buffers)
+static_assert(2 * 4 * NW * 64 * 4 <= OFF_ROWS && OFF_ROWS + 2 * TB * D <= OFF_LH, "the merge fits in the row buffers");
+static_assert(2 * LDS * 4 <= 160 * 1024, "two workgroups per compute unit");
+static_assert(THREADS == 2 * kPadPartial, "two threads per pad-gradient channel");
+
+typedef __attribute__((address_space(3))) void lds_void;
+
+// Row r holds its 16-byte piece p at position p ^ (r & 15): the 16 rows a 16-lane read of one
+// piece touches cover all 64 banks.
+__device__ __forceinline__ int swz(int r) { return r & 15; }
+
+// wait until this wave's outstanding global loads (and the LDS writes of its direct loads) are done
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8)); }
+
+__device__ __forceinline__ float dot4(const float4& x, const float4& y, float s) {
+    s = __builtin_fmaf(x.x, y.x, s);
+    s = __builtin_fmaf(x.y, y.y, s);
+    s = __builtin_fmaf(x.z, y.z, s);
+    return __builtin_fmaf(x.w, y.w, s);
+}
+__device__ __forceinline__ float4 load4(__amdgpu_buffer_rsrc_t r, unsigned off) {
+    return __builtin_bit_cast(float4, bload16(r, off));
+}
+__device__ __forceinline__ float4 lds4(const float* p) { return *reinterpret_cast<const float4*>(p); }
+
+// What both roles know about their block, and the lane's operand addresses in a chunk's rows.
 struct Block {
-    int head, blk, win, b;
+    int b, win, blk, head;
+    WindowRect wr;
+    int n;                      // tokens of the window
+    long long n_pad;            // virtual key slots of its canvas square (KV-token mode)
+    WindowAddr addr;
+    long long q_base, kv_base, pad_elems;   // elements to the window's first token, and to the pad row
+    __amdgpu_buffer_rsrc_t qr, orr, dor, kr, vr, lr;
+    int tid, lane, li, h, wave, tt, sh;
+    int rb;                     // row read: piece h D/8 + j of row 32 sh + li at rb ^ 4 j
+    int cb[4];                  // column read of row 32 sh + 8 q + 4 h + j: see column()
 };
 
-__device__ __forceinline__ Block decode(const SwinArgs& a) {
-    long long id = blockIdx.x;
-    Block r;
-    r.head = (int)(id % a.heads);
-    id /= a.heads;
-    r.blk = (int)(id % a.nqb);
-    id /= a.nqb;
-    r.win = (int)(id % a.n_windows);
-    r.b = (int)(id / a.n_windows);
-    return r;
+// element 32 db + li of row 32 sh + 8 (r / 4) + 4 h + r % 4 of a chunk's rows
+__device__ __forceinline__ float column(const Block& k, const float* rows, int r, int db) {
+    const int q = r >> 2;
+    return rows[k.cb[r & 3] + 8 * q * D + 32 * (db ^ (q & 1))];
 }
 
-// element offset of window-local token t (t < n) from the start of a batch entry's head
-__device__ __forceinline__ long long token_elems(const SwinArgs& a, const WindowRect& wr, int t) {
-    const int r = t / wr.cols;
-    return (wr.tok0 + (long long)r * wr.W + (t - r * wr.cols)) * a.tok_stride;
+// the lane's half of 32 row-read channels: acc += <streamed row, reg> over them
+__device__ __forceinline__ floatx16 row_product(const Block& k, const float* rows, const float (&reg)[D / 2],
+                                                floatx16 acc) {
+#pragma unroll
+    for (int j = 0; j < D / 8; ++j) {
+        const float4 x = lds4(rows + (k.rb ^ (4 * j)));
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.x, reg[4 * j], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.y, reg[4 * j + 1], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.z, reg[4 * j + 2], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.w, reg[4 * j + 3], acc, 0, 0, 0);
+    }
+    return acc;
 }
 
-__device__ __forceinline__ long long token_index(const WindowRect& wr, int t) {
-    const int r = t / wr.cols;
-    return wr.tok0 + (long long)r * wr.W + (t - r * wr.cols);
+// Rows 16 w .. 16 w + 15 of the chunk starting at window-local token `base` straight into the
+// swizzled LDS rows `dst`; rows past the window: zeros.
+__device__ __forceinline__ void load_rows(const Block& k, __amdgpu_buffer_rsrc_t src, float* dst, int base) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = 16 * k.wave + 4 * i + (k.lane >> 4);
+        const int p = (k.lane & 15) ^ swz(r);
+        const unsigned off = base + r < k.n ? k.addr(base + r) + 16 * p : kOutside;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (lds_void*)(dst + (16 * k.wave + 4 * i) * D), 16, off, 0, 0, 0);
+    }
 }
 
-__global__ __launch_bounds__(THREADS) void swin_bwd_f32_dq_kernel(SwinBwdArgs ba) {
+// the lane's half (channels h D/2 ..) of a token's row, times `scale`
+__device__ __forceinline__ void load_half(const Block& k, __amdgpu_buffer_rsrc_t src, int t, float (&reg)[D / 2],
+                                          float scale) {
+    const unsigned off = t < k.n ? k.addr(t) + k.h * (D / 2) * 4 : kOutside;
+#pragma unroll
+    for (int i = 0; i < D / 8; ++i) {
+        const float4 x = load4(src, off + 16 * i);
+        reg[4 * i] = x.x * scale;
+        reg[4 * i + 1] = x.y * scale;
+        reg[4 * i + 2] = x.z * scale;
+        reg[4 * i + 3] = x.w * scale;
+    }
+}
+
+// The two waves of a tile add their accumulators: each hands over the row groups that its
+// partner finishes (of every channel block 2 sh', 2 sh' + 1) ...
+__device__ __forceinline__ void hand_over(const Block& k, float4* exch, const floatx16 (&acc)[2]) {
+#pragma unroll
+    for (int db = 0; db < 2; ++db)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int lo = 4 * i, hi = 8 + 4 * i;
+            exch[((k.wave * 2 + db) * 2 + i) * 64 + k.lane] =
+                k.sh ? make_float4(acc[db][lo], acc[db][lo + 1], acc[db][lo + 2], acc[db][lo + 3])
+                     : make_float4(acc[db][hi], acc[db][hi + 1], acc[db][hi + 2], acc[db][hi + 3]);
+        }
+}
+// ... and finishes its own: (sum + w[ch] extra) * scale into the tile's staged rows.  The sum is wave
+// sh = 0's part plus wave sh = 1's in both.
+__device__ __forceinline__ void finish(const Block& k, const float4* exch, float* rows, const floatx16 (&acc)[2],
+                                       float scale, float extra, const float* w) {
+    const int row = TL * k.tt + k.li;
+#pragma unroll
+    for (int db = 0; db < 2; ++db)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int lo = 4 * i, hi = 8 + 4 * i, ch = 32 * db + 8 * (2 * k.sh + i) + 4 * k.h;
+            const float4 y = exch[(((k.wave ^ 1) * 2 + db) * 2 + i) * 64 + k.lane];
+            float4 x = k.sh ? make_float4(acc[db][hi], acc[db][hi + 1], acc[db][hi + 2], acc[db][hi + 3])
+                            : make_float4(acc[db][lo], acc[db][lo + 1], acc[db][lo + 2], acc[db][lo + 3]);
+            x = make_float4(x.x + y.x, x.y + y.y, x.z + y.z, x.w + y.w);
+            if (w != nullptr) {
+                const float4 e = lds4(w + ch);
+                x = make_float4(__builtin_fmaf(extra, e.x, x.x), __builtin_fmaf(extra, e.y, x.y),
+                                __builtin_fmaf(extra, e.z, x.z), __builtin_fmaf(extra, e.w, x.w));
+            }
+            *reinterpret_cast<float4*>(rows + row * D + 4 * ((ch >> 2) ^ swz(row))) =
+                make_float4(x.x * scale, x.y * scale, x.z * scale, x.w * scale);
+        }
+}
+// the block's staged rows to their tokens, whole 256-byte rows
+__device__ __forceinline__ void store_rows(const Block& k, const float* rows, __amdgpu_buffer_rsrc_t dst) {
+#pragma unroll
+    for (int i = k.tid; i < TB * ROWP; i += THREADS) {
+        const int r = i / ROWP, p = i % ROWP, t = TB * k.blk + r;
+        const u32x4 v = *reinterpret_cast<const u32x4*>(rows + r * D + 4 * (p ^ swz(r)));
+        __builtin_amdgcn_raw_buffer_store_b128(v, dst, t < k.n ? k.addr(t) + 16 * p : kOutside, 0, 0);
+    }
+}
+
+template <bool KVPAD>
+__device__ __forceinline__ void key_role(const SwinBwdArgs& ba, const Block& k, float* smem) {
     const SwinArgs& a = ba.f;
-    __shared__ __attribute__((aligned(16))) float Kf[CH * D];
-    __shared__ __attribute__((aligned(16))) float Vf[CH * D];
-    __shared__ float Pp[THREADS], Sp[THREADS];
-
-    const Block blk = decode(a);
-    const WindowRect wr = window_rect<true>(a, blk.win);
-    const int n = wr.rows * wr.cols;
-    const int q_begin = blk.blk * kQueryBlock;
-    const long long n_pad = (long long)a.window * a.window - n;
-    const bool has_pad = a.pad_mode == 1 && n_pad > 0;
-    // KV-token mode: every block writes its share of the pad token's gradient (zero when the
-    // window has no virtual slots or the block no queries), so the reduction reads a dense array
-    float* ws_entry = a.pad_mode == 1
-        ? ba.ws + (((long long)blk.b * a.heads + blk.head) * a.n_windows + blk.win) * a.nqb * kPadPartial +
-              (long long)blk.blk * kPadPartial
-        : nullptr;
-    if (ws_entry != nullptr && !(has_pad && q_begin < n) && threadIdx.x < kPadPartial) ws_entry[threadIdx.x] = 0.f;
-    if (q_begin >= n) return;
-    const int nq = min(kQueryBlock, n - q_begin);
-
-    const long long qoff = (long long)blk.b * a.q_batch_stride + blk.head * D;
-    const long long kvoff = (long long)blk.b * a.kv_batch_stride + blk.head * D;
-    const float* qg = static_cast<const float*>(a.q) + qoff;
-    const float* og = static_cast<const float*>(ba.out) + qoff;
-    const float* dog = static_cast<const float*>(ba.dout) + qoff;
-    float* dqg = static_cast<float*>(ba.dq) + qoff;
-    const float* kg = static_cast<const float*>(a.k) + kvoff;
-    const float* vg = static_cast<const float*>(a.v) + kvoff;
-    const long long lse0 = ((long long)blk.b * a.heads + blk.head) * a.L;
-
-    const int tid = threadIdx.x;
-    const int t = q_begin + tid;
-    const bool active = t < n;
-    const int tq = active ? t : n - 1;
-
-    float qv[D], dov[D], dq[D];
-    float Dv = 0.f;
-    {
-        const float* qr = qg + token_elems(a, wr, tq);
-        const float* orow = og + token_elems(a, wr, tq);
-        const float* dr = dog + token_elems(a, wr, tq);
-        for (int i = 0; i < D; ++i) {
-            qv[i] = qr[i] * a.scale_log2;   // logits in the exp2 domain
-            dov[i] = dr[i];
-            Dv = fmaf(dr[i], orow[i], Dv);
-            dq[i] = 0.f;
-        }
+    const int key0 = TB * k.blk;
+    if (key0 >= k.n) return;   // the window has fewer blocks
+    const bool pad_here = KVPAD && k.n_pad > 0 && k.blk == 0;
+    if (KVPAD && k.blk == 0 && !pad_here && k.tid < kPadPartial) {   // the reduction reads a dense array
+        const long long e = ((long long)k.b * a.heads + k.head) * a.n_windows + k.win;
+        ba.ws[e * kPadPartial + k.tid] = 0.f;
     }
-    const float lse2 = ba.lse[lse0 + token_index(wr, tq)] * kLog2e;
+    const bool work = key0 + TL * k.tt < k.n;
+    const int nch = (k.n + CH - 1) / CH;
+    float* padkv = smem + OFF_PADKV;
 
-    for (int kc0 = 0; kc0 < n; kc0 += CH) {
-        const int ck = min(CH, n - kc0);
+    // the row this thread prepares of every chunk (4 threads per row: pieces qq, qq + 4, ...)
+    const int pr = 16 * k.wave + (k.lane >> 2), qq = k.lane & 3;
+    float4 ov[4];
+    float lse;
+    auto issue = [&](int c) {
+        const int buf = c & 1, t = CH * c + pr;
+        load_rows(k, k.qr, smem + OFF_X + buf * BUF, CH * c);
+        load_rows(k, k.dor, smem + OFF_Y + buf * BUF, CH * c);
+        const unsigned off = t < k.n ? k.addr(t) + 16 * qq : kOutside;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ov[i] = load4(k.orr, off + 64 * i);
+        lse = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                            k.lr, t < k.n ? 4 * k.addr.token(t, (unsigned)k.wr.W) : kOutside, 0, 0));
+    };
+    issue(0);
+    float kreg[D / 2], vreg[D / 2];
+    load_half(k, k.kr, key0 + TL * k.tt + k.li, kreg, a.scale_log2);
+    load_half(k, k.vr, key0 + TL * k.tt + k.li, vreg, 1.f);
+    if (pad_here) {
+        if (k.tid < 2 * D)
+            padkv[k.tid] = static_cast<const float*>(k.tid < D ? a.k : a.v)[k.pad_elems + (k.tid & (D - 1))];
         __syncthreads();
-        for (int i = tid; i < CH * (D / 4); i += THREADS) {
-            const int key = i / (D / 4), part = i % (D / 4);
-            float4 kx = make_float4(0.f, 0.f, 0.f, 0.f), vx = kx;
-            if (key < ck) {
-                const long long off = token_elems(a, wr, kc0 + key) + part * 4;
-                kx = *reinterpret_cast<const float4*>(kg + off);
-                vx = *reinterpret_cast<const float4*>(vg + off);
-            }
-            *reinterpret_cast<float4*>(&Kf[key * D + part * 4]) = kx;
-            *reinterpret_cast<float4*>(&Vf[key * D + part * 4]) = vx;
-        }
-        __syncthreads();
-        for (int j = 0; j < ck; ++j) {
-            const float* kr = &Kf[j * D];
-            const float* vr = &Vf[j * D];
-            float s = 0.f, dp = 0.f;
-            for (int i = 0; i < D; ++i) {
-                s = fmaf(qv[i], kr[i], s);
-                dp = fmaf(dov[i], vr[i], dp);
-            }
-            const float ds = exp2f(s - lse2) * (dp - Dv);
-            for (int i = 0; i < D; ++i) dq[i] = fmaf(ds, kr[i], dq[i]);
-        }
     }
+    const float log2_npad = pad_here ? log2f((float)k.n_pad) : 0.f;
+    float pad_sum = 0.f;   // thread (half, channel): its half of each chunk's rows, over the chunks
 
-    float p_pad = 0.f, ds_pad = 0.f;
-    if (has_pad) {
-        const long long prow = (long long)blk.b * a.kv_batch_stride + a.L * a.tok_stride + blk.head * D;
-        const float* kp = static_cast<const float*>(a.k) + prow;
-        const float* vp = static_cast<const float*>(a.v) + prow;
-        float s = 0.f, dp = 0.f;
-        for (int i = 0; i < D; ++i) {
-            s = fmaf(qv[i], kp[i], s);
-            dp = fmaf(dov[i], vp[i], dp);
-        }
-        p_pad = exp2f(s + log2f((float)n_pad) - lse2);
-        ds_pad = p_pad * (dp - Dv);
-        for (int i = 0; i < D; ++i) dq[i] = fmaf(ds_pad, kp[i], dq[i]);
-    }
-
-    if (active) {
-        float* row = dqg + token_elems(a, wr, t);
-        for (int i = 0; i < D; i += 4)
-            *reinterpret_cast<float4*>(row + i) =
-                make_float4(dq[i] * ba.scale, dq[i + 1] * ba.scale, dq[i + 2] * ba.scale, dq[i + 3] * ba.scale);
-    }
-
-    if (has_pad) {
-        // this block's share of the pad token's gradient:
-        //   dk_pad += c sum_i dS_ip q_i,  dv_pad += sum_i P_ip dO_i   (over the block's queries)
-        Pp[tid] = active ? p_pad : 0.f;
-        Sp[tid] = active ? ds_pad : 0.f;
-        __syncthreads();
-        if (tid < kPadPartial) {
-            const bool is_k = tid < D;
-            const int ch = is_k ? tid : tid - D;
-            const float* src = is_k ? qg : dog;
-            const float* wgt = is_k ? Sp : Pp;
-            float acc = 0.f;
-            for (int i = 0; i < nq; ++i) acc = fmaf(wgt[i], src[token_elems(a, wr, q_begin + i) + ch], acc);
-            ws_entry[tid] = is_k ? acc * ba.scale : acc;
-        }
-    }
-}
-
-// KIND 0: dv_j = sum_i P_ij dO_i;  KIND 1: dk_j = c sum_i dS_ij q_i
-template <int KIND>
-__global__ __launch_bounds__(THREADS) void swin_bwd_f32_dkv_kernel(SwinBwdArgs ba) {
-    const SwinArgs& a = ba.f;
-    __shared__ __attribute__((aligned(16))) float Qf[CH * D];
-    __shared__ __attribute__((aligned(16))) float Gf[CH * D];   // dO rows
-    __shared__ float Lf[CH], Df[CH];
-
-    const Block blk = decode(a);
-    const WindowRect wr = window_rect<true>(a, blk.win);
-    const int n = wr.rows * wr.cols;
-    const int k_begin = blk.blk * kQueryBlock;
-    if (k_begin >= n) return;
-
-    const long long qoff = (long long)blk.b * a.q_batch_stride + blk.head * D;
-    const long long kvoff = (long long)blk.b * a.kv_batch_stride + blk.head * D;
-    const float* qg = static_cast<const float*>(a.q) + qoff;
-    const float* og = static_cast<const float*>(ba.out) + qoff;
-    const float* dog = static_cast<const float*>(ba.dout) + qoff;
-    const float* kg = static_cast<const float*>(a.k) + kvoff;
-    const float* vg = static_cast<const float*>(a.v) + kvoff;
-    float* outg = static_cast<float*>(KIND == 0 ? ba.dv : ba.dk) + kvoff;
-    const long long lse0 = ((long long)blk.b * a.heads + blk.head) * a.L;
-
-    const int tid = threadIdx.x;
-    const int t = k_begin + tid;
-    const bool active = t < n;
-    const int tk = active ? t : n - 1;
-
-    float kv[D], vv[KIND == 1 ? D : 1], acc[D];
-    {
-        const float* kr = kg + token_elems(a, wr, tk);
-        for (int i = 0; i < D; ++i) {
-            kv[i] = kr[i] * a.scale_log2;
-            acc[i] = 0.f;
-        }
-        if constexpr (KIND == 1) {
-            const float* vr = vg + token_elems(a, wr, tk);
-            for (int i = 0; i < D; ++i) vv[i] = vr[i];
-        }
-    }
-
-    for (int qc0 = 0; qc0 < n; qc0 += CH) {
-        const int cq = min(CH, n - qc0);
-        __syncthreads();
-        for (int i = tid; i < CH * (D / 4); i += THREADS) {
-            const int qi = i / (D / 4), part = i % (D / 4);
-            float4 qx = make_float4(0.f, 0.f, 0.f, 0.f), gx = qx;
-            if (qi < cq) {
-                const long long off = token_elems(a, wr, qc0 + qi) + part * 4;
-                qx = *reinterpret_cast<const float4*>(qg + off);
-                gx = *reinterpret_cast<const float4*>(dog + off);
-            }
-            *reinterpret_cast<float4*>(&Qf[qi * D + part * 4]) = qx;
-            *reinterpret_cast<float4*>(&Gf[qi * D + part * 4]) = gx;
-        }
-        if (tid < CH) {
-            float lse2 = 0.f, dd = 0.f;
-            if (tid < cq) {
-                lse2 = ba.lse[lse0 + token_index(wr, qc0 + tid)] * kLog2e;
-                if constexpr (KIND == 1) {
-                    const long long off = token_elems(a, wr, qc0 + tid);
-                    for (int i = 0; i < D; ++i) dd = fmaf(dog[off + i], og[off + i], dd);
+    floatx16 dkT[2] = {floatx16{}, floatx16{}}, dvT[2] = {floatx16{}, floatx16{}};
+    for (int c = 0; c < nch; ++c) {
+        const int buf = c & 1;
+        float* Qs = smem + OFF_X + buf * BUF;
+        float* Gs = smem + OFF_Y + buf * BUF;
+        float* LH = smem + OFF_LH + buf * CH;
+        float* LL = smem + OFF_LL + buf * CH;
+        float* ND = smem + OFF_ND + buf * CH;
+        float* PP = smem + OFF_PP + buf * CH;
+        float* DSP = smem + OFF_DSP + buf * CH;
+        // ---- the wave's own rows of this chunk: LSE log2(e), D and the pad token's P and dS
+        wait_loads();
+        {
+            float dd = 0.f, zp = 0.f, dp = 0.f;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int p = qq + 4 * i, at = pr * D + 4 * (p ^ swz(pr));
+                const float4 g4 = lds4(Gs + at);
+                dd = dot4(g4, ov[i], dd);
+                if (pad_here) {
+                    zp = dot4(lds4(Qs + at), lds4(padkv + 4 * p), zp);
+                    dp = dot4(g4, lds4(padkv + D + 4 * p), dp);
                 }
             }
-            Lf[tid] = lse2;
-            Df[tid] = dd;
+            dd += __shfl_xor(dd, 1);
+            dd += __shfl_xor(dd, 2);
+            const float lh = lse * kLog2eHi;
+            const float ll = __builtin_fmaf(lse, kLog2eLo, __builtin_fmaf(lse, kLog2eHi, -lh));
+            if (pad_here) {
+                zp += __shfl_xor(zp, 1);
+                zp += __shfl_xor(zp, 2);
+                dp += __shfl_xor(dp, 1);
+                dp += __shfl_xor(dp, 2);
+                const float p = CH * c + pr < k.n ? exp2f(__builtin_fmaf(zp, a.scale_log2, log2_npad - lh) - ll) : 0.f;
+                if (qq == 0) {
+                    PP[pr] = p;
+                    DSP[pr] = p * (dp - dd);
+                }
+            }
+            if (qq == 0) {
+                LH[pr] = lh;
+                LL[pr] = ll;
+                ND[pr] = -dd;
+            }
         }
-        __syncthreads();
-        for (int i = 0; i < cq; ++i) {
-            const float* qr = &Qf[i * D];
-            const float* gr = &Gf[i * D];
-            float s = 0.f;
-            for (int e = 0; e < D; ++e) s = fmaf(kv[e], qr[e], s);
-            const float p = exp2f(s - Lf[i]);
-            if constexpr (KIND == 0) {
-                for (int e = 0; e < D; ++e) acc[e] = fmaf(p, gr[e], acc[e]);
-            } else {
-                float dp = 0.f;
-                for (int e = 0; e < D; ++e) dp = fmaf(vv[e], gr[e], dp);
-                const float ds = p * (dp - Df[i]);
-                for (int e = 0; e < D; ++e) acc[e] = fmaf(ds, qr[e], acc[e]);
+        __syncthreads();   // the chunk is published; every wave is done with the previous one
+        if (c + 1 < nch) issue(c + 1);
+        if (pad_here) {
+            // thread (half, ch) sums channel ch of dS_p q (ch < 64) or P_p dO over rows 32 half ..
+            // + 31 (rows past the window have P = dS = 0)
+            const int ch = k.tid & (D - 1), half = k.tid / kPadPartial;
+            const bool is_k = (k.tid & (kPadPartial - 1)) < D;
+            const float* w = is_k ? DSP : PP;
+            const float* rows = is_k ? Qs : Gs;
+            float s4[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+            for (int i = 0; i < CH / 2; i += 4)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int r = CH / 2 * half + i + j;
+                    s4[j] = __builtin_fmaf(w[r], rows[r * D + 4 * ((ch >> 2) ^ swz(r)) + (ch & 3)], s4[j]);
+                }
+            pad_sum += (s4[0] + s4[1]) + (s4[2] + s4[3]);
+        }
+        if (!work || CH * c + TL * k.sh >= k.n) continue;
+        // ---- the streamed tile (register r: query 8 (r / 4) + 4 h + r % 4) against the wave's keys
+        const floatx16 s = row_product(k, Qs, kreg, floatx16{});
+        floatx16 dp;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float4 d4 = lds4(ND + TL * k.sh + 8 * i + 4 * k.h);
+            dp[4 * i] = d4.x;
+            dp[4 * i + 1] = d4.y;
+            dp[4 * i + 2] = d4.z;
+            dp[4 * i + 3] = d4.w;
+        }
+        dp = row_product(k, Gs, vreg, dp);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float4 h4 = lds4(LH + TL * k.sh + 8 * i + 4 * k.h), l4 = lds4(LL + TL * k.sh + 8 * i + 4 * k.h);
+            const float hv[4] = {h4.x, h4.y, h4.z, h4.w}, lv[4] = {l4.x, l4.y, l4.z, l4.w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int r = 4 * i + j;
+                const float p = __builtin_amdgcn_exp2f((s[r] - hv[j]) - lv[j]);
+                const float ds = p * dp[r];
+#pragma unroll
+                for (int db = 0; db < 2; ++db) {
+                    dvT[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(column(k, Gs, r, db), p, dvT[db], 0, 0, 0);
+                    dkT[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(column(k, Qs, r, db), ds, dkT[db], 0, 0, 0);
+                }
             }
         }
     }
-
-    if (active) {
-        const float sc = KIND == 1 ? ba.scale : 1.f;
-        float* row = outg + token_elems(a, wr, t);
-        for (int i = 0; i < D; i += 4)
-            *reinterpret_cast<float4*>(row + i) =
-                make_float4(acc[i] * sc, acc[i + 1] * sc, acc[i + 2] * sc, acc[i + 3] * sc);
+    if (pad_here) smem[OFF_PADW + k.tid] = pad_sum;
+    __syncthreads();   // the row buffers are free; the pad sums are complete
+    if (pad_here && k.tid < kPadPartial) {
+        const long long e = ((long long)k.b * a.heads + k.head) * a.n_windows + k.win;
+        const float x = smem[OFF_PADW + k.tid] + smem[OFF_PADW + kPadPartial + k.tid];
+        ba.ws[e * kPadPartial + k.tid] = k.tid < D ? x * ba.scale : x;
     }
+    float4* exch_k = reinterpret_cast<float4*>(smem);
+    float4* exch_v = exch_k + NW * 4 * 64;
+    float* rows_k = smem + OFF_ROWS;
+    float* rows_v = rows_k + TB * D;
+    if (work) {
+        hand_over(k, exch_k, dkT);
+        hand_over(k, exch_v, dvT);
+    }
+    __syncthreads();
+    if (work) {
+        finish(k, exch_k, rows_k, dkT, ba.scale, 0.f, nullptr);
+        finish(k, exch_v, rows_v, dvT, 1.f, 0.f, nullptr);
+    }
+    __syncthreads();
+    const long long kv_bytes = ((long long)a.B * a.kv_batch_stride - k.kv_base) * 4;
+    store_rows(k, rows_k, make_rsrc(static_cast<float*>(ba.dk) + k.kv_base, kv_bytes));
+    store_rows(k, rows_v, make_rsrc(static_cast<float*>(ba.dv) + k.kv_base, kv_bytes));
+}
+
+template <bool KVPAD>
+__device__ __forceinline__ void query_role(const SwinBwdArgs& ba, const Block& k, float* smem) {
+    const SwinArgs& a = ba.f;
+    const int q0 = TB * k.blk;
+    if (q0 >= k.n) return;
+    const bool has_pad = KVPAD && k.n_pad > 0;
+    const int q = q0 + TL * k.tt + k.li;   // the lane's query
+    const bool work = q0 + TL * k.tt < k.n;
+    const int nch = (k.n + CH - 1) / CH;
+    float* padkv = smem + OFF_PADKV;
+    auto issue = [&](int c) {
+        load_rows(k, k.kr, smem + OFF_X + (c & 1) * BUF, CH * c);
+        load_rows(k, k.vr, smem + OFF_Y + (c & 1) * BUF, CH * c);
+    };
+    issue(0);
+    float qreg[D / 2], greg[D / 2];
+    load_half(k, k.qr, q, qreg, a.scale_log2);
+    load_half(k, k.dor, q, greg, 1.f);
+    float dd = 0.f;
+    {
+        const unsigned off = q < k.n ? k.addr(q) + k.h * (D / 2) * 4 : kOutside;
+#pragma unroll
+        for (int i = 0; i < D / 8; ++i)
+            dd = dot4(make_float4(greg[4 * i], greg[4 * i + 1], greg[4 * i + 2], greg[4 * i + 3]),
+                      load4(k.orr, off + 16 * i), dd);
+    }
+    dd = xhalf_sum(dd);
+    const float lse = __builtin_bit_cast(
+        float, __builtin_amdgcn_raw_buffer_load_b32(k.lr, q < k.n ? 4 * k.addr.token(q, (unsigned)k.wr.W) : kOutside, 0, 0));
+    const float lh = lse * kLog2eHi;
+    const float ll = __builtin_fmaf(lse, kLog2eLo, __builtin_fmaf(lse, kLog2eHi, -lh));
+    // pad token as key: dS_p = n_pad exp(c <q, k_pad> - LSE) (<dO, v_pad> - D); dq gets dS_p k_pad
+    float dsp = 0.f;
+    if (has_pad) {
+        if (k.tid < 2 * D)
+            padkv[k.tid] = static_cast<const float*>(k.tid < D ? a.k : a.v)[k.pad_elems + (k.tid & (D - 1))];
+        __syncthreads();
+        float zp = 0.f, dp = 0.f;
+#pragma unroll
+        for (int i = 0; i < D / 2; ++i) {
+            zp = __builtin_fmaf(qreg[i], padkv[k.h * (D / 2) + i], zp);
+            dp = __builtin_fmaf(greg[i], padkv[D + k.h * (D / 2) + i], dp);
+        }
+        zp = xhalf_sum(zp);
+        dp = xhalf_sum(dp);
+        dsp = exp2f((zp + (log2f((float)k.n_pad) - lh)) - ll) * (dp - dd);
+    }
+
+    floatx16 dqT[2] = {floatx16{}, floatx16{}};
+    for (int c = 0; c < nch; ++c) {
+        const float* Ks = smem + OFF_X + (c & 1) * BUF;
+        const float* Vs = smem + OFF_Y + (c & 1) * BUF;
+        wait_loads();
+        __syncthreads();   // the chunk is published; every wave is done with the previous one
+        if (c + 1 < nch) issue(c + 1);
+        const int nv = k.n - (CH * c + TL * k.sh);   // keys of the wave's tile
+        if (!work || nv <= 0) continue;
+        floatx16 s = row_product(k, Ks, qreg, floatx16{});
+        floatx16 dp;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) dp[r] = -dd;
+        dp = row_product(k, Vs, greg, dp);
+        // register r: key 8 (r / 4) + 4 h + r % 4; rows past the window are zero, and P is cleared so
+        // that no infinity meets them
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const float p = __builtin_amdgcn_exp2f((s[r] - lh) - ll);
+            s[r] = (8 * (r >> 2) + 4 * k.h + (r & 3) < nv ? p : 0.f) * dp[r];
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+#pragma unroll
+            for (int db = 0; db < 2; ++db)
+                dqT[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(column(k, Ks, r, db), s[r], dqT[db], 0, 0, 0);
+    }
+    __syncthreads();   // the row buffers are free
+    float4* exch = reinterpret_cast<float4*>(smem);
+    float* rows = smem + OFF_ROWS;
+    if (work) hand_over(k, exch, dqT);
+    __syncthreads();
+    if (work) finish(k, exch, rows, dqT, ba.scale, dsp, has_pad ? padkv : nullptr);
+    __syncthreads();
+    store_rows(k, rows, make_rsrc(static_cast<float*>(ba.dq) + k.q_base, ((long long)a.B * a.q_batch_stride - k.q_base) * 4));
+}
+
+// Workgroup id -> (unit, block, role), unit = (batch entry, window, head): the workgroups of one
+// unit get ids that are equal mod 8, one after the other, so that they run on one XCD and all but
+// the first find the window's rows in its L2.
+template <bool KVPAD>
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void swin_bwd_f32_kernel(SwinBwdArgs ba) {
+    const SwinArgs& a = ba.f;
+    __shared__ __attribute__((aligned(16))) float smem[LDS];
+    const unsigned id = blockIdx.x + kGridX * blockIdx.y;
+    const unsigned rest = id >> 3;
+    const unsigned g = ba.div_2nbb.div(rest);
+    const unsigned j = rest - g * (2u * (unsigned)ba.nbb);
+    const unsigned unit = (g << 3) + (id & 7u);
+    if (unit >= (unsigned)a.n_units) return;
+    Block k;
+    k.blk = (int)(j >> 1);
+    const unsigned i2 = a.div_heads.div(unit);
+    k.head = (int)(unit - i2 * (unsigned)a.heads);
+    const unsigned i3 = a.div_nwin.div(i2);
+    k.win = (int)(i2 - i3 * (unsigned)a.n_windows);
+    k.b = (int)i3;
+    k.wr = window_rect<true>(a, k.win);
+    k.n = k.wr.rows * k.wr.cols;
+    k.n_pad = (long long)a.window * a.window - k.n;
+
+    const long long win_elems = k.wr.tok0 * a.tok_stride + k.head * D;
+    k.q_base = (long long)k.b * a.q_batch_stride + win_elems;
+    k.kv_base = (long long)k.b * a.kv_batch_stride + win_elems;
+    k.pad_elems = (long long)k.b * a.kv_batch_stride + a.L * a.tok_stride + k.head * D;
+    const long long q_bytes = ((long long)a.B * a.q_batch_stride - k.q_base) * 4;
+    const long long kv_bytes = ((long long)a.B * a.kv_batch_stride - k.kv_base) * 4;
+    k.qr = make_rsrc(static_cast<const float*>(a.q) + k.q_base, q_bytes);
+    k.orr = make_rsrc(static_cast<const float*>(ba.out) + k.q_base, q_bytes);
+    k.dor = make_rsrc(static_cast<const float*>(ba.dout) + k.q_base, q_bytes);
+    k.kr = make_rsrc(static_cast<const float*>(a.k) + k.kv_base, kv_bytes);
+    k.vr = make_rsrc(static_cast<const float*>(a.v) + k.kv_base, kv_bytes);
+    const long long lse_base = ((long long)k.b * a.heads + k.head) * a.L + k.wr.tok0;
+    const long long lse_total = (long long)a.B * a.heads * a.L;
+    k.lr = make_rsrc(ba.lse + lse_base, (lse_total - lse_base) * 4);
+    k.addr.init(k.wr.cols, (unsigned)((long long)k.wr.W * a.tok_stride * 4), (unsigned)(a.tok_stride * 4));
+
+    k.tid = (int)threadIdx.x;
+    k.lane = k.tid & 63;
+    k.li = k.lane & 31;
+    k.h = k.lane >> 5;
+    k.wave = __builtin_amdgcn_readfirstlane(k.tid >> 6);
+    k.tt = k.wave >> 1;
+    k.sh = k.wave & 1;
+    k.rb = (TL * k.sh + k.li) * D + 4 * ((k.h * (D / 8)) ^ swz(k.li));
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const int row = 4 * k.h + c;
+        k.cb[c] = (TL * k.sh + row) * D + 4 * ((k.li >> 2) ^ swz(row)) + (k.li & 3);
+    }
+    if (j & 1u)
+        query_role<KVPAD>(ba, k, smem);
+    else
+        key_role<KVPAD>(ba, k, smem);
 }
 
 // One workgroup per (batch entry, head): row L of dk and dv = the sum of the partials of
@@ -314,16 +555,16 @@ __global__ __launch_bounds__(kRedSlices * kPadPartial) void swin_bwd_pad_reduce_
 
 hipError_t launch_swin_bwd_f32(const SwinBwdArgs& a, hipStream_t stream) {
     SwinBwdArgs args = a;
+    args.nbb = (a.f.n_max + TB - 1) / TB;
+    args.div_2nbb = FastDiv::make(2u * (unsigned)args.nbb);
     void* params[] = {&args};
-    const dim3 grid((unsigned)a.f.n_groups), block(THREADS);
-    hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(&swin_bwd_f32_dq_kernel), grid, block,
-                                   params, 0, stream);
-    if (e != hipSuccess) return e;
-    e = hipLaunchKernel(reinterpret_cast<const void*>(&swin_bwd_f32_dkv_kernel<0>), grid, block, params, 0,
-                        stream);
-    if (e != hipSuccess) return e;
-    return hipLaunchKernel(reinterpret_cast<const void*>(&swin_bwd_f32_dkv_kernel<1>), grid, block, params,
-                           0, stream);
+    const void* fn = a.f.pad_mode == 1 ? reinterpret_cast<const void*>(&swin_bwd_f32_kernel<true>)
+                                       : reinterpret_cast<const void*>(&swin_bwd_f32_kernel<false>);
+    // up to eight times as many workgroups as the host's limit counts (blocks of 256 tokens): ids
+    // past one row of the launch grid go on along y
+    const int64_t groups = 16 * (int64_t)args.nbb * ((a.f.n_units + 7) / 8);
+    const unsigned gy = (unsigned)((groups + kGridX - 1) / kGridX);
+    return hipLaunchKernel(fn, dim3(gy > 1 ? kGridX : (unsigned)groups, gy), dim3(THREADS), params, 0, stream);
 }
 
 hipError_t launch_swin_bwd_pad_reduce(const SwinBwdArgs& a, int elem_bytes, hipStream_t stream) {

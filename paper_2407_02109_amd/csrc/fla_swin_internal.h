@@ -114,10 +114,10 @@ constexpr int kPadPartial = 2 * kHeadDim;   // floats per pad-gradient partial: 
 // Backward pass: the forward's geometry plus the gradient tensors.  Inputs q, k, v (in f),
 // out, dout and lse; outputs dq, dk, dv.  ws holds one pad-gradient partial per (b, head,
 // window, block) in KV-token mode: ws[((b * heads + head) * n_windows + win) * pad_blocks
-// + blk][0:64] = dk part, [64:128] = dv part.  Every block writes its entry (zero when its
-// window has no virtual slots), and the pad reduce kernel sums them.  The bf16 kernel's
-// blocks are kBwdBlock tokens (pad_blocks = nbb), the fp32 kernels' kQueryBlock tokens
-// (pad_blocks = f.nqb).
+// + blk][0:64] = dk part, [64:128] = dv part.  Every entry is written (zero when its window
+// has no virtual slots), and the pad reduce kernel sums them.  The bf16 block kernel writes
+// one per block of kBwdBlock tokens (pad_blocks = nbb), the bf16 one-window kernel and the fp32
+// kernel one per window (pad_blocks = 1).
 struct SwinBwdArgs {
     SwinArgs f;
     const void* out;
@@ -128,8 +128,8 @@ struct SwinBwdArgs {
     void* dv;
     float* ws;
     int pad_blocks;             // blocks per window in the layout of ws
-    int nbb;                    // bf16: kBwdBlock-token blocks of the largest window
-    FastDiv div_2nbb;           // bf16 workgroup decode: division by 2 * nbb
+    int nbb;                    // kBwdBlock-token blocks of the largest window (the fp32 launch sets its own)
+    FastDiv div_2nbb;           // workgroup decode: division by 2 * nbb
     int64_t n_units;            // bf16: B * heads * windows
     float scale;                // 1 / sqrt(head_dim)
     int store_nt;               // bf16: gradient rows stored non-temporally (see store_row)
