@@ -22,11 +22,23 @@
 //           to t; no recurrence, y overwritten in place.
 // Two passes of exponentials over the data, where scanning the laid-out copies takes r.
 //
-// A wave takes 64 channels of one chunk: a lane holds one channel's N states in registers;
-// x (pass C: y1) and Delta of a token are one coalesced 256-byte read per wave, and B_t, C_t,
-// the same for every channel, are wave-uniform reads.  Bound by the vector ALU (one
-// exponential per token, channel and state in each of passes A and C).
+// A workgroup takes 64 channels of one chunk, a lane one channel; its SPLIT waves share the N
+// states (N / SPLIT each in a lane's registers) and add their shares of y through LDS, four tokens
+// at a time.  x (pass C: y1) and Delta of a token are one coalesced 256-byte read per wave; B_t and
+// C_t, the same for every channel, are wave-uniform reads into scalar registers.
+// Bound by the vector ALU: per (token, channel, state) pass A issues six plain operations and an
+// exponential, pass C three and an exponential.  Measured with the operands in registers, a plain
+// operation on vector registers takes 2.6 to 3.5 cycles of a SIMD with four or more waves on it
+// (8 with one), one with a scalar operand 4.4 to 5, an exponential 8.5: about 30 and 20.4 cycles,
+// 510 us for 65536 tokens x 768 channels x 32 states.  One wave per group ran them at 434 + 289 us
+// (vector ALU busy 79 and 73%: waits for the scalar rows and a tail of unequal waves), four waves
+// in pass A and one in pass C at 400 + 264 us; 4096 tokens, 768 groups for 1024 SIMDs: 118 -> 74 us
+// a call with eight waves.  Taking the products over (tokens or states) x channels from the matrix
+// cores (4x4x1 outer products, 9.5 cycles for four) was no faster: 690 us a call.
 #include "fla_cycle_scan.h"
+
+#include <type_traits>
+
 #include "fla_swin_device.h"
 
 namespace fla {
@@ -47,72 +59,145 @@ __device__ __forceinline__ void load_row(const float* p, float (&w)[N]) {
     for (int n = 0; n < N; ++n) w[n] = q[n];
 }
 
-template <int N>
-__global__ __launch_bounds__(64) void cycle_scan_chunks(CycleArgs c) {
-    const int cg = blockIdx.x % c.cgroups;
-    const int rest = blockIdx.x / c.cgroups;
-    const int chunk = rest % c.nch;
-    const int b = rest / c.nch;
-    const int ch = cg * 64 + (int)threadIdx.x;
-    const bool ok = ch < c.d;
-    const int chs = ok ? ch : c.d - 1;
+// What a wave of a scan pass works on: states ns .. ns + N / SPLIT - 1 of 64 channels of one chunk.
+// Rows of x, Delta and y are addressed by a buffer resource at the row's first channel of the 64,
+// whose range check drops the lanes past the last channel.
+template <int N, int SPLIT>
+struct ScanWave {
+    static constexpr int NW = N / SPLIT;                                  // states per lane
+    static constexpr int PER = SPLIT < kTokens ? kTokens / SPLIT : 1;     // tokens of a group this wave stores
+    static constexpr int PAIR = N <= 8 || SPLIT > 1 ? 2 : 1;               // tokens whose rows are read together
+    int lane, wave, b, chunk, t0, t1, ns, ch0, live_ch;
+    size_t rb;
+    __device__ __forceinline__ explicit ScanWave(const CycleArgs& c) {
+        const int cg = blockIdx.x % c.cgroups;
+        const int rest = blockIdx.x / c.cgroups;
+        chunk = rest % c.nch;
+        b = rest / c.nch;
+        lane = (int)threadIdx.x & 63;
+        wave = SPLIT > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) : 0;
+        ns = wave * NW;
+        ch0 = cg * 64;
+        live_ch = min(64, c.d - ch0);
+        t0 = chunk * c.T;
+        t1 = min(t0 + c.T, c.L);
+        rb = (size_t)b * c.L;
+    }
+    __device__ __forceinline__ bool ok() const { return lane < live_ch; }
+    __device__ __forceinline__ int channel() const { return ch0 + min(lane, live_ch - 1); }
+    // the lane's channel of token t of a [B, L, d] tensor
+    __device__ __forceinline__ __amdgpu_buffer_rsrc_t row(const CycleArgs& c, const float* p, int t) const {
+        return make_rsrc(p + (rb + t) * c.d + ch0, 4 * live_ch);
+    }
+    __device__ __forceinline__ float load(const CycleArgs& c, const float* p, int t) const {
+        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(row(c, p, t), 4u * (unsigned)lane, 0, 0));
+    }
+    __device__ __forceinline__ void store(const CycleArgs& c, float* p, int t, float v) const {
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), row(c, p, t), 4u * (unsigned)lane, 0, 0);
+    }
+};
+
+// f over the groups of kTokens tokens of [t0, t1): f(group's first token, tokens of it that exist),
+// the whole groups with a compile-time count
+template <typename F>
+__device__ __forceinline__ void for_groups(int t0, int t1, F&& f) {
+    const int tfull = t0 + (t1 - t0) / kTokens * kTokens;
+    for (int tg = t0; tg < tfull; tg += kTokens) f(tg, std::integral_constant<int, kTokens>{});
+    if (tfull < t1) f(tfull, t1 - tfull);
+}
+
+// The waves' shares of y of a group of tokens, added in wave order: wave w gets its PER tokens from
+// PER w on in acc[0 ..].  One barrier per call: `red` alternates between two buffers.
+template <int SPLIT, int PER>
+__device__ __forceinline__ void add_shares(float (*red)[kTokens][64], int wave, int lane, float (&acc)[kTokens]) {
+    if constexpr (SPLIT > 1) {
+#pragma unroll
+        for (int j = 0; j < kTokens; ++j) red[wave][j][lane] = acc[j];
+        __syncthreads();
+        if (PER * wave < kTokens)
+#pragma unroll
+            for (int j = 0; j < PER; ++j) {
+                float s = red[0][PER * wave + j][lane];
+#pragma unroll
+                for (int w = 1; w < SPLIT; ++w) s += red[w][PER * wave + j][lane];
+                acc[j] = s;
+            }
+    }
+}
+
+template <int N, int SPLIT>
+__global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(1, SPLIT >= 4 ? 6 : 8)))
+void cycle_scan_chunks(CycleArgs c) {
+    using W = ScanWave<N, SPLIT>;
+    constexpr int NW = W::NW, PER = W::PER, PAIR = W::PAIR;
+    __shared__ float red[2][SPLIT][kTokens][64];
+    const W w(c);
     // the state scaled by a, g = a h, takes one product less per step:
     // g <- dA g + (dA - 1) u b; the output C . h = sum_n (C[n] / a[n]) g[n]
-    float a2[N], ia[N], g[N];
+    float a2[NW], ia[NW], g[NW];
+    const float* ap = c.A + (size_t)w.channel() * N + w.ns;
 #pragma unroll
-    for (int n = 0; n < N; ++n) {
-        const float a = c.A[(size_t)chs * N + n];
+    for (int n = 0; n < NW; ++n) {
+        const float a = ap[n];
         a2[n] = a * kLog2e;
         ia[n] = 1.f / a;
         g[n] = 0.f;
     }
-    const int t0 = chunk * c.T;
-    const int t1 = min(t0 + c.T, c.L);
-    const float* xp = c.x + (size_t)b * c.L * c.d + chs;
-    const float* dp = c.delta + (size_t)b * c.L * c.d + chs;
-    const size_t rb = (size_t)b * c.L;
     float sd = 0.f;
-    auto step = [&](int t, float u, float dl) {
-        const size_t row = rb + t;
-        float w[N], cv[N];
-        load_row<N>(c.Bm + row * N, w);
-        load_row<N>(c.Cm + row * N, cv);
-        float acc[2] = {0.f, 0.f};   // two sums, two dependency chains
-#pragma unroll
-        for (int n = 0; n < N; ++n) {
-            const float dA = __builtin_amdgcn_exp2f(dl * a2[n]);
-            const float z = u * w[n];
-            g[n] = __builtin_fmaf(dA, g[n] + z, -z);   // dA g + (dA - 1) z
-            acc[n & 1] = __builtin_fmaf(cv[n] * ia[n], g[n], acc[n & 1]);
-        }
-        sd += dl;
-        // lanes past the last channel compute channel d - 1 from the same inputs: the value
-        // they store there is the same
-        c.y[row * c.d + chs] = acc[0] + acc[1];
-    };
-    // whole groups of kTokens tokens: their x and Delta loaded together, one wait per group
-    const int tfull = t0 + (t1 - t0) / kTokens * kTokens;
-    for (int tg = t0; tg < tfull; tg += kTokens) {
-        float uu[kTokens], dd[kTokens];
+    int buf = 0;
+    for_groups(w.t0, w.t1, [&](int tg, auto live) {
+        float u[kTokens], dl[kTokens], acc[kTokens];
 #pragma unroll
         for (int j = 0; j < kTokens; ++j) {
-            uu[j] = xp[(size_t)(tg + j) * c.d];
-            dd[j] = dp[(size_t)(tg + j) * c.d];
+            u[j] = dl[j] = acc[j] = 0.f;
+            if (j < live) {
+                u[j] = w.load(c, c.x, tg + j);
+                dl[j] = w.load(c, c.delta, tg + j);
+            }
         }
 #pragma unroll
-        for (int j = 0; j < kTokens; ++j) step(tg + j, uu[j], dd[j]);
-    }
-    for (int t = tfull; t < t1; ++t) step(t, xp[(size_t)t * c.d], dp[(size_t)t * c.d]);
-    if (ok) {
+        for (int j0 = 0; j0 < kTokens; j0 += PAIR) {
+            if (j0 >= live) break;
+            float wv[PAIR][NW], cv[PAIR][NW];
+#pragma unroll
+            for (int p = 0; p < PAIR; ++p) {
+                const size_t row = w.rb + (tg + min(j0 + p, live - 1));
+                load_row<NW>(c.Bm + row * N + w.ns, wv[p]);
+                load_row<NW>(c.Cm + row * N + w.ns, cv[p]);
+            }
+#pragma unroll
+            for (int p = 0; p < PAIR; ++p) {
+                const int j = j0 + p;
+                if (j >= live) break;
+                float y2[2] = {0.f, 0.f};   // two sums, two dependency chains
+#pragma unroll
+                for (int n = 0; n < NW; ++n) {
+                    const float dA = __builtin_amdgcn_exp2f(dl[j] * a2[n]);
+                    const float z = u[j] * wv[p][n];
+                    g[n] = __builtin_fmaf(dA, g[n] + z, -z);   // dA g + (dA - 1) z
+                    y2[n & 1] = __builtin_fmaf(cv[p][n] * ia[n], g[n], y2[n & 1]);
+                }
+                acc[j] = y2[0] + y2[1];
+                sd += dl[j];
+            }
+        }
+        add_shares<SPLIT, PER>(red[buf], w.wave, w.lane, acc);
+        buf ^= 1;
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+            if (PER * w.wave + j < live) w.store(c, c.y, tg + PER * w.wave + j, acc[j]);
+    });
+    if (w.ok()) {
+        const int ch = w.channel();
         // A is read in full before any store (a store to the workspace could alias it, so
         // interleaved, every load would wait for the store before it)
-        float a[N];
+        float a[NW];
 #pragma unroll
-        for (int n = 0; n < N; ++n) a[n] = c.A[(size_t)ch * N + n];
-        float* hw = c.ws_h + (((size_t)b * c.nch + chunk) * c.d + ch) * N;
+        for (int n = 0; n < NW; ++n) a[n] = ap[n];
+        float* hw = c.ws_h + (((size_t)w.b * c.nch + w.chunk) * c.d + ch) * N + w.ns;
 #pragma unroll
-        for (int n = 0; n < N; ++n) hw[n] = g[n] / a[n];
-        c.ws_s[((size_t)b * c.nch + chunk) * c.d + ch] = sd;
+        for (int n = 0; n < NW; ++n) hw[n] = g[n] / a[n];
+        if (w.wave == 0) c.ws_s[((size_t)w.b * c.nch + w.chunk) * c.d + ch] = sd;
     }
 }
 
@@ -199,60 +284,65 @@ __global__ __launch_bounds__(256) void cycle_scan_carries(CycleArgs c) {
     }
 }
 
-template <int N>
-__global__ __launch_bounds__(64) void cycle_scan_outputs(CycleArgs c) {
-    const int cg = blockIdx.x % c.cgroups;
-    const int rest = blockIdx.x / c.cgroups;
-    const int chunk = rest % c.nch;
-    const int b = rest / c.nch;
-    const int ch = cg * 64 + (int)threadIdx.x;
-    const bool ok = ch < c.d;
-    const int chs = ok ? ch : c.d - 1;
-    const float* hw = c.ws_h + (((size_t)b * c.nch + chunk) * c.d + chs) * N;
-    float a2[N], e[N];
+template <int N, int SPLIT>
+__global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(1, N == 32 && SPLIT == 1 ? 3 : 8)))
+void cycle_scan_outputs(CycleArgs c) {
+    using W = ScanWave<N, SPLIT>;
+    constexpr int NW = W::NW, PER = W::PER, PAIR = W::PAIR;
+    __shared__ float red[2][SPLIT][kTokens][64];
+    const W w(c);
+    const float* ap = c.A + (size_t)w.channel() * N + w.ns;
+    const float* hw = c.ws_h + (((size_t)w.b * c.nch + w.chunk) * c.d + w.channel()) * N + w.ns;
+    float a2[NW], e[NW];
 #pragma unroll
-    for (int n = 0; n < N; ++n) {
-        a2[n] = c.A[(size_t)chs * N + n] * kLog2e;
+    for (int n = 0; n < NW; ++n) {
+        a2[n] = ap[n] * kLog2e;
         e[n] = hw[n];   // E_c
     }
     const float r = (float)c.repeats;
-    const int t0 = chunk * c.T;
-    const int t1 = min(t0 + c.T, c.L);
-    const size_t rb = (size_t)b * c.L;
-    float* yp = c.y + rb * c.d + chs;
-    const float* dp = c.delta + rb * c.d + chs;
     float cum = 0.f;   // sum of Delta from the chunk's start to t
-    auto step = [&](int t, float y1, float dl) {
-        const size_t row = rb + t;
-        float cv[N];
-        load_row<N>(c.Cm + row * N, cv);
-        cum += dl;
-        float acc[2] = {r * y1, 0.f};
-#pragma unroll
-        for (int n = 0; n < N; ++n) {
-            const float p = __builtin_amdgcn_exp2f(a2[n] * cum);   // decay from the chunk's start
-            acc[n & 1] = __builtin_fmaf(cv[n], p * e[n], acc[n & 1]);
-        }
-        // each lane reads y1 and then writes y at its own address; lanes past the last
-        // channel, which repeat channel d - 1, must not write there (the lane of channel d - 1
-        // may already have replaced the y1 they read)
-        if (ok) yp[(size_t)t * c.d] = acc[0] + acc[1];
-    };
-    const int tfull = t0 + (t1 - t0) / kTokens * kTokens;
-    for (int tg = t0; tg < tfull; tg += kTokens) {
-        float yy[kTokens], dd[kTokens];
+    int buf = 0;
+    for_groups(w.t0, w.t1, [&](int tg, auto live) {
+        float dl[kTokens], y1[PER], acc[kTokens];
 #pragma unroll
         for (int j = 0; j < kTokens; ++j) {
-            yy[j] = yp[(size_t)(tg + j) * c.d];
-            dd[j] = dp[(size_t)(tg + j) * c.d];
+            dl[j] = acc[j] = 0.f;
+            if (j < live) dl[j] = w.load(c, c.delta, tg + j);
         }
 #pragma unroll
-        for (int j = 0; j < kTokens; ++j) step(tg + j, yy[j], dd[j]);
-    }
-    for (int t = tfull; t < t1; ++t) step(t, yp[(size_t)t * c.d], dp[(size_t)t * c.d]);
+        for (int j = 0; j < PER; ++j)   // the tokens this wave stores
+            y1[j] = PER * w.wave + j < live ? w.load(c, c.y, tg + PER * w.wave + j) : 0.f;
+#pragma unroll
+        for (int j0 = 0; j0 < kTokens; j0 += PAIR) {
+            if (j0 >= live) break;
+            float cv[PAIR][NW];
+#pragma unroll
+            for (int p = 0; p < PAIR; ++p)
+                load_row<NW>(c.Cm + (w.rb + (tg + min(j0 + p, live - 1))) * N + w.ns, cv[p]);
+#pragma unroll
+            for (int p = 0; p < PAIR; ++p) {
+                const int j = j0 + p;
+                if (j >= live) break;
+                cum += dl[j];
+                float y2[2] = {0.f, 0.f};
+#pragma unroll
+                for (int n = 0; n < NW; ++n) {
+                    const float dec = __builtin_amdgcn_exp2f(a2[n] * cum);   // decay from the chunk's start
+                    y2[n & 1] = __builtin_fmaf(cv[p][n], dec * e[n], y2[n & 1]);
+                }
+                acc[j] = y2[0] + y2[1];
+            }
+        }
+        add_shares<SPLIT, PER>(red[buf], w.wave, w.lane, acc);
+        buf ^= 1;
+        // each lane reads y1 and then writes y at its own address
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+            if (PER * w.wave + j < live) w.store(c, c.y, tg + PER * w.wave + j, __builtin_fmaf(r, y1[j], acc[j]));
+    });
 }
 
-template <int N>
+template <int N, int SPA, int SPC>
 hipError_t launch_n(const CycleArgs& a, hipStream_t stream) {
     CycleArgs args = a;
     // carry pass: up to 8 segments of at least kBatch chunks per (channel, state)
@@ -260,16 +350,16 @@ hipError_t launch_n(const CycleArgs& a, hipStream_t stream) {
     while (args.seg < 8 && (long long)args.seg * kBatch < a.nch) args.seg *= 2;
     void* params[] = {&args};
     const long long scan_groups = (long long)a.B * a.nch * a.cgroups;
-    hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(&cycle_scan_chunks<N>), dim3((unsigned)scan_groups),
-                                   dim3(64), params, 0, stream);
+    hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(&cycle_scan_chunks<N, SPA>),
+                                   dim3((unsigned)scan_groups), dim3(64 * SPA), params, 0, stream);
     if (e != hipSuccess) return e;
     const long long per_wg = 256 / args.seg;
     const long long carry_groups = (long long)a.B * (((long long)a.d * a.N + per_wg - 1) / per_wg);
     e = hipLaunchKernel(reinterpret_cast<const void*>(&cycle_scan_carries), dim3((unsigned)carry_groups), dim3(256),
                         params, 0, stream);
     if (e != hipSuccess) return e;
-    return hipLaunchKernel(reinterpret_cast<const void*>(&cycle_scan_outputs<N>), dim3((unsigned)scan_groups),
-                           dim3(64), params, 0, stream);
+    return hipLaunchKernel(reinterpret_cast<const void*>(&cycle_scan_outputs<N, SPC>), dim3((unsigned)scan_groups),
+                           dim3(64 * SPC), params, 0, stream);
 }
 
 }  // namespace
@@ -277,13 +367,28 @@ hipError_t launch_n(const CycleArgs& a, hipStream_t stream) {
 bool cycle_states_supported(int N) { return N == 1 || N == 2 || N == 4 || N == 8 || N == 16 || N == 32; }
 
 hipError_t launch_cycle_scan(const CycleArgs& a, hipStream_t stream) {
+    // Waves that share one chunk's states, by the number of (chunk, 64 channels) groups.  Few groups
+    // leave SIMDs without a wave (one wave alone issues at half the rate of two): more waves per
+    // group.  Many: fewer, since every wave reads the group's x and Delta and joins the sum.
+    // Measured per call, 768 channels, us, split 1 / 2 / 4 / 8: 32 states, 4096 tokens (768 groups)
+    // 107 / 100 / 73 / 72; 32768 tokens (1536) 502 / 499 / 371 / 444; 65536 tokens (3072) 697 / 809 /
+    // 679 / 873, and 661 with pass A at 4 and pass C at 1.  16 states: 65536 tokens 454 / 422 / 470 /
+    // 649; 20000 tokens of 384 channels (474) 222 / 228 / 151 / 148; 2 x 65536 of 1024 (8192) 930 /
+    // 999 / 1166 / 1607.  Up to 8 states one wave holds them all.
+    const long long groups = (long long)a.B * a.nch * a.cgroups;
     switch (a.N) {
-        case 1: return launch_n<1>(a, stream);
-        case 2: return launch_n<2>(a, stream);
-        case 4: return launch_n<4>(a, stream);
-        case 8: return launch_n<8>(a, stream);
-        case 16: return launch_n<16>(a, stream);
-        case 32: return launch_n<32>(a, stream);
+        case 1: return launch_n<1, 1, 1>(a, stream);
+        case 2: return launch_n<2, 1, 1>(a, stream);
+        case 4: return launch_n<4, 1, 1>(a, stream);
+        case 8: return launch_n<8, 1, 1>(a, stream);
+        case 16:
+            return groups >= 6144   ? launch_n<16, 1, 1>(a, stream)
+                   : groups >= 2048 ? launch_n<16, 2, 2>(a, stream)
+                                    : launch_n<16, 4, 4>(a, stream);
+        case 32:
+            return groups >= 3072   ? launch_n<32, 4, 1>(a, stream)
+                   : groups >= 1024 ? launch_n<32, 4, 4>(a, stream)
+                                    : launch_n<32, 8, 8>(a, stream);
         default: return hipErrorInvalidValue;
     }
 }

@@ -85,6 +85,11 @@ inline void __builtin_amdgcn_raw_buffer_store_b128(emu_u32x4 v, __amdgpu_buffer_
         }
 }
 
+inline void __builtin_amdgcn_raw_buffer_store_b32(unsigned v, __amdgpu_buffer_rsrc_t r, unsigned off, int soff, int) {
+    const unsigned long long o = (unsigned long long)off + (unsigned)soff;
+    if (o + 4 <= r.bytes) std::memcpy(r.base + o, &v, 4);
+}
+
 // D = A B + C, A 32 x 16, B 16 x 32, fp32 accumulation.  Lane l supplies row l % 32 of A and
 // column l % 32 of B, elements 8 (l / 32) .. + 7 of the reduction; it receives column l % 32
 // of D, rows 8 (r / 4) + 4 (l / 32) + r % 4 for r = 0 .. 15.
@@ -206,7 +211,6 @@ inline void __builtin_amdgcn_raw_ptr_buffer_load_lds(__amdgpu_buffer_rsrc_t r, _
     }
 }
 inline void __builtin_amdgcn_s_waitcnt(int) { emu_wave_barrier(); }
-inline void __builtin_amdgcn_sched_barrier(int) {}   // orders the compiler's schedule only
 
 inline int __builtin_amdgcn_readfirstlane(int x) {
     int* s = reinterpret_cast<int*>(emu_wave_slots());
