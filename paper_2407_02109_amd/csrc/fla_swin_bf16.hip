@@ -1,6 +1,7 @@
 // Flash Swin attention forward, bf16 storage, gfx950 (CDNA4) matrix cores.
 //
-// One workgroup = one (batch entry, window, block of up to 256 queries, head).  The
+// One workgroup = one (batch entry, window, block of up to 256 queries, head) (128 or 64 queries
+// in small launches of long windows, see SPLIT).  The
 // window's rectangle comes from integer arithmetic on the shifted-window geometry
 // (HRSAM Sec. 3.3 / App. A): no index table, no reordered copy.  Its real tokens are
 // taken in row-major order inside the rectangle (Eq. nonshift), so the key set is dense:
@@ -38,6 +39,9 @@
 // of the window's row and column positions in a per-workgroup LDS table (windows of at most
 // 32 x 32 tokens; wider ones evaluate them per rotated piece), so a rotated copy of q and k
 // never goes through HBM.  The pad token has no position and is not rotated.
+#include <algorithm>
+#include <type_traits>
+
 #include "fla_swin_device.h"
 
 namespace fla {
@@ -67,6 +71,7 @@ struct Cfg {
     static constexpr int VPT = (VUNITS + THREADS - 1) / THREADS;   // V pieces per thread
     static constexpr int WAVES = D > 64 ? 2 : 4;
 };
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 constexpr float kLazyThreshold = 8.f;   // exp2-domain headroom before the max is raised
 constexpr float kLn2 = 0.693147180559945309f;
 
@@ -175,11 +180,16 @@ __device__ __forceinline__ void rope_rotate8_at(uint16_t (&x)[8], float pos, con
 
 constexpr int kRopeTab = 32;   // window rows / columns covered by the per-workgroup RoPE table
 
-template <bool MULTI, bool ROPE, int D>
+// SPLIT waves share the keys of a query tile (a block is 256 / SPLIT queries): wave w takes tile w mod 8/SPLIT
+// against every SPLIT-th key tile from w / (8/SPLIT) on, and the shares are merged at the end (their
+// maxima, sums and O^T through LDS).  SPLIT 1 is the form above; launch_swin_fwd_bf16 says when
+// more pays.
+template <bool MULTI, bool ROPE, int D, int SPLIT>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(Cfg<D>::WAVES, Cfg<D>::WAVES)))
 void swin_fwd_bf16_kernel(SwinArgs a) {
     static_assert(!ROPE || D == kHeadDim, "RoPE: head_dim 64 only");
     constexpr int KS = Cfg<D>::KS, TPR = Cfg<D>::TPR, TPR_LOG = Cfg<D>::TPR_LOG, RPP = Cfg<D>::RPP;
+    constexpr int NQT = THREADS / 64 / SPLIT;   // query tiles per workgroup
     __shared__ __attribute__((aligned(16))) uint16_t Ks[KC * KS];
     __shared__ __attribute__((aligned(16))) uint16_t Vt[D * VS];
     // RoPE: (cos, sin) of the window's row positions [0][r][j] and column positions [1][c][j]
@@ -220,7 +230,7 @@ void swin_fwd_bf16_kernel(SwinArgs a) {
 
     const WindowRect wr = window_rect<MULTI>(a, win);
     const int n = wr.rows * wr.cols;
-    const int q_begin = qblk * kQueryBlock;
+    const int q_begin = qblk * (QW * NQT);
     if (q_begin >= n) return;   // whole workgroup: this window has fewer query blocks
 
     const long long n_pad = (long long)a.window * a.window - n;
@@ -253,11 +263,13 @@ void swin_fwd_bf16_kernel(SwinArgs a) {
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
+    const int wave = SPLIT > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
+    const int qt = SPLIT > 1 ? wave % NQT : wave;    // query tile
+    const int ks = SPLIT > 1 ? wave / NQT : 0;       // share of the key tiles
     const int li = lane & 31;
     const int h = lane >> 5;
 
-    const int wq0 = q_begin + wave * QW;
+    const int wq0 = q_begin + qt * QW;
     const int nq = min(QW, n - wq0);   // queries of this wave (<= 0: the wave only loads)
 
     // ---- Q in registers, B-operand layout: lane holds q[query li][16*st + 8*h .. +8]
@@ -415,10 +427,14 @@ void swin_fwd_bf16_kernel(SwinArgs a) {
         // the rest (at most the last two: past the keys, or holding the pad token) do
         auto attend_range = [&](int t_begin, int t_end) {
             const int t_plain = min(t_end, t_begin + max(0, (n - kc0 - t_begin) / KT) * KT);
-            for (int t0 = t_begin; t0 < t_plain; t0 += KT)
+            int t_tail = t_plain;
+            for (int t0 = t_begin + KT * ks; t0 < t_plain; t0 += KT * SPLIT) {
                 attend_tile<D, false>(Ks, Vt, t0, kc0, nk, n, pad_bias_raw, qop, o, m_run, neg_mc, l_run,
                                    a.scale_log2, lane);
-            for (int t0 = t_plain; t0 < t_end; t0 += KT)
+            }
+            if constexpr (SPLIT > 1)   // this wave's first tile from t_plain on
+                t_tail += KT * ((ks + SPLIT - (t_plain - t_begin) / KT % SPLIT) % SPLIT);
+            for (int t0 = t_tail; t0 < t_end; t0 += KT * SPLIT)
                 attend_tile<D, true>(Ks, Vt, t0, kc0, nk, n, pad_bias_raw, qop, o, m_run, neg_mc, l_run,
                                   a.scale_log2, lane);
         };
@@ -434,8 +450,52 @@ void swin_fwd_bf16_kernel(SwinArgs a) {
     //      wave is past its last tile) so that the stores are whole rows: D/8 lanes per row
     //      (8 per 128-byte row at D = 64), 16 bytes per lane.
     __syncthreads();
+    // SPLIT > 1: shares 1 .. of a query tile leave O^T, m and l in LDS, and the wave of share 0 adds
+    // them to its own.  Slot 4 on and the staged result rows are in V^T's space, behind each other.
+    float l_own = 0.f;
+    uint16_t* stage = Ks;
+    if constexpr (SPLIT > 1) {
+        constexpr int SLOT = D * QW * 2;                 // uint16 of one wave's O^T (fp32)
+        constexpr int SLOTS = (SPLIT - 1) * NQT;
+        constexpr int STAGE = (SLOTS > 4 ? SLOTS - 4 : 0) * SLOT, ML = STAGE + NQT * QW * KS;
+        static_assert(4 * SLOT <= KC * KS && ML + SLOTS * 64 * 4 <= D * VS && ML % 4 == 0, "LDS of the merge");
+        stage = Vt + STAGE;
+        float2* ml = reinterpret_cast<float2*>(Vt + ML);
+        auto slot = [&](int i) { return reinterpret_cast<floatx4*>(i < 4 ? Ks + i * SLOT : Vt + (i - 4) * SLOT) + lane; };
+        l_own = xhalf_sum(l_run);
+        if (ks > 0 && nq > 0) {
+            floatx4* x = slot(wave - NQT);
+            for (int db = 0; db < D / 32; ++db)
+                for (int rg = 0; rg < 4; ++rg)
+                    x[64 * (4 * db + rg)] = floatx4{o[db][4 * rg], o[db][4 * rg + 1], o[db][4 * rg + 2], o[db][4 * rg + 3]};
+            ml[(wave - NQT) * 64 + lane] = make_float2(m_run, l_own);
+        }
+        __syncthreads();
+        if (ks > 0) return;
+        if (nq > 0) {
+            float m_all = m_run;
+            for (int i = 0; i < SPLIT - 1; ++i) m_all = __builtin_fmaxf(m_all, ml[(NQT * i + qt) * 64 + lane].x);
+            // (equal maxima: weight 1, also where both are -inf)
+            const float w_own = m_run == m_all ? 1.f : __builtin_amdgcn_exp2f((m_run - m_all) * a.scale_log2);
+            l_own *= w_own;
+            for (int db = 0; db < D / 32; ++db) o[db] *= w_own;
+#pragma unroll 1
+            for (int i = 0; i < SPLIT - 1; ++i) {
+                const float2 s = ml[(NQT * i + qt) * 64 + lane];
+                const float w = s.x == m_all ? 1.f : __builtin_amdgcn_exp2f((s.x - m_all) * a.scale_log2);
+                l_own = __builtin_fmaf(s.y, w, l_own);
+                const floatx4* x = slot(NQT * i + qt);
+                for (int db = 0; db < D / 32; ++db)
+                    for (int rg = 0; rg < 4; ++rg) {
+                        const floatx4 y = x[64 * (4 * db + rg)];
+                        for (int u = 0; u < 4; ++u) o[db][4 * rg + u] = __builtin_fmaf(y[u], w, o[db][4 * rg + u]);
+                    }
+            }
+            m_run = m_all;
+        }
+    }
     if (nq > 0) {
-        const float lsum = xhalf_sum(l_run);
+        const float lsum = SPLIT > 1 ? l_own : xhalf_sum(l_run);
         const float inv = 1.f / lsum;
         if (a.lse != nullptr && h == 0 && li < nq) {
             // log of the softmax denominator over the logits q.k / sqrt(d), natural units
@@ -443,7 +503,7 @@ void swin_fwd_bf16_kernel(SwinArgs a) {
                                   addr.token(wq0 + li, (unsigned)wr.W);
             a.lse[row] = (m_run * a.scale_log2 + log2f(lsum)) * kLn2;
         }
-        uint16_t* orow = Ks + (wave * QW + li) * KS;
+        uint16_t* orow = stage + (qt * QW + li) * KS;
         for (int db = 0; db < D / 32; ++db)
             for (int rg = 0; rg < 4; ++rg) {
                 bf16x4 r4;
@@ -455,7 +515,7 @@ void swin_fwd_bf16_kernel(SwinArgs a) {
         constexpr int rows = 64 / TPR;   // rows per store instruction
         for (int i = 0; i < QW / rows; ++i) {
             const int r = rows * i + (lane >> TPR_LOG);
-            const uint4 v = *reinterpret_cast<const uint4*>(Ks + (wave * QW + r) * KS + 8 * part);
+            const uint4 v = *reinterpret_cast<const uint4*>(stage + (qt * QW + r) * KS + 8 * part);
             const unsigned off = r < nq ? addr(wq0 + r) + 16 * part : kOutside;   // tail rows: dropped
             // non-temporal: the output is not read again by this layer, and its lines should not
             // displace inputs that a layer fitting the last-level cache reads again
@@ -466,22 +526,67 @@ void swin_fwd_bf16_kernel(SwinArgs a) {
 
 }  // namespace
 
-template <int D>
-const void* plain_kernel(const SwinArgs& a) {
-    return a.n_grids > 1 ? reinterpret_cast<const void*>(&swin_fwd_bf16_kernel<true, false, D>)
-                         : reinterpret_cast<const void*>(&swin_fwd_bf16_kernel<false, false, D>);
+// Blocks of kQueryBlock queries that a launch really has (a window has as many as its own tokens need),
+// counted up to the first window that takes them past `most`.
+int64_t query_blocks(const SwinArgs& a, int64_t most) {
+    int64_t blocks = 0;
+    const int64_t per_block = (int64_t)a.B * a.heads;
+    for (int g = 0; g < a.n_grids; ++g) {
+        const GridDesc& G = a.grid[g];
+        if (G.H < 1 || G.W < 1) continue;
+        for (int64_t y0 = -(int64_t)a.origin; y0 < G.H; y0 += a.window) {
+            const int64_t rows = std::min<int64_t>(y0 + a.window, G.H) - std::max<int64_t>(y0, 0);
+            for (int64_t x0 = -(int64_t)a.origin; x0 < G.W; x0 += a.window) {
+                const int64_t cols = std::min<int64_t>(x0 + a.window, G.W) - std::max<int64_t>(x0, 0);
+                blocks += (rows * cols + kQueryBlock - 1) / kQueryBlock * per_block;
+                if (blocks > most) return blocks;
+            }
+        }
+    }
+    return blocks;
+}
+
+template <int SPLIT>
+const void* kernel(const SwinArgs& a) {
+    const bool multi = a.n_grids > 1;
+    auto plain = [&](auto d) {
+        constexpr int D = decltype(d)::value;
+        return multi ? reinterpret_cast<const void*>(&swin_fwd_bf16_kernel<true, false, D, SPLIT>)
+                     : reinterpret_cast<const void*>(&swin_fwd_bf16_kernel<false, false, D, SPLIT>);
+    };
+    if (a.rope)   // head_dim 64 only (the host checks)
+        return multi ? reinterpret_cast<const void*>(&swin_fwd_bf16_kernel<true, true, kHeadDim, SPLIT>)
+                     : reinterpret_cast<const void*>(&swin_fwd_bf16_kernel<false, true, kHeadDim, SPLIT>);
+    return a.head_dim == 32    ? plain(std::integral_constant<int, 32>{})
+           : a.head_dim == 128 ? plain(std::integral_constant<int, 128>{})
+                               : plain(std::integral_constant<int, kHeadDim>{});
 }
 
 hipError_t launch_swin_fwd_bf16(const SwinArgs& a, hipStream_t stream) {
     SwinArgs args = a;
     void* params[] = {&args};
-    const void* fn;
-    if (a.rope)   // head_dim 64 only (the host checks)
-        fn = a.n_grids > 1 ? reinterpret_cast<const void*>(&swin_fwd_bf16_kernel<true, true, kHeadDim>)
-                           : reinterpret_cast<const void*>(&swin_fwd_bf16_kernel<false, true, kHeadDim>);
-    else
-        fn = a.head_dim == 32 ? plain_kernel<32>(a) : a.head_dim == 128 ? plain_kernel<128>(a) : plain_kernel<64>(a);
-    return hipLaunchKernel(fn, dim3((unsigned)fwd_bf16_groups(a)), dim3(THREADS), params, 0, stream);
+    // Waves that share the keys of a query tile, for windows of more than 256 tokens by the number of
+    // 256-query blocks.  Few blocks leave CUs idle while each block's waves run a long window's tiles
+    // one after the other, two waves per SIMD: SPLIT times as many blocks of 256 / SPLIT queries, whose
+    // waves take 1 / SPLIT of the tiles each, while they get a CU of their own.  More blocks than
+    // that would only stage every window SPLIT times as often.  Measured per call, us, SPLIT 1 / 2 / 4 (64x64
+    // tokens, heads of 64, window 64, shift 32, unless said): 3 heads (48 blocks) 25.6 / 18.6 / 15.3;
+    // 6 heads (96) 25.9 / 19.2 / 20.7, with RoPE 29.9 / 23.2 / 26.2; 8 heads (128) 25.9 / 19.5 / 20.9;
+    // 12 heads (192) 26.5 / 26.9 / 30.7; 24 heads (384) 41.0 / 41.9 / 56.1.  Heads of 128: 3 39.4 / 29.1
+    // / 24.2, 6 39.8 / 29.9 / 45.8.  24 heads of 32, 32x32 tokens, window 32 (96) 19.9 / 14.4 / 15.4.
+    // 400-token windows: 3 heads (75) 13.1 / 12.4 / 12.4, 6 heads (150) 13.3 / 13.6 / 15.3.
+    int split = 1;
+    if (a.xcd_group) {
+        const int64_t blocks = query_blocks(a, 128);
+        split = blocks <= 64 ? 4 : blocks <= 128 ? 2 : 1;
+    }
+    if (split > 1) {
+        const int qb = kQueryBlock / split;
+        args.nqb = (a.n_max + qb - 1) / qb;
+        args.div_nqb = FastDiv::make((unsigned)args.nqb);
+    }
+    const void* fn = split == 4 ? kernel<4>(a) : split == 2 ? kernel<2>(a) : kernel<1>(a);
+    return hipLaunchKernel(fn, dim3((unsigned)fwd_bf16_groups(args)), dim3(THREADS), params, 0, stream);
 }
 
 }  // namespace fla
