@@ -307,8 +307,11 @@ __device__ __forceinline__ void key_role(const SwinBwdArgs& ba, const Block& k, 
                 }
             pad_sum += (s4[0] + s4[1]) + (s4[2] + s4[3]);
         }
-        if (!work || CH * c + TL * k.sh >= k.n) continue;
-        // ---- the streamed tile (register r: query 8 (r / 4) + 4 h + r % 4) against the wave's keys
+        const int nv = k.n - (CH * c + TL * k.sh);   // queries of the wave's tile
+        if (!work || nv <= 0) continue;
+        // ---- the streamed tile (register r: query 8 (r / 4) + 4 h + r % 4) against the wave's keys;
+        // rows past the window are zero, and P is cleared there: a key with an infinite component
+        // makes their logit 0 * inf
         const floatx16 s = row_product(k, Qs, kreg, floatx16{});
         floatx16 dp;
 #pragma unroll
@@ -327,7 +330,8 @@ __device__ __forceinline__ void key_role(const SwinBwdArgs& ba, const Block& k, 
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int r = 4 * i + j;
-                const float p = __builtin_amdgcn_exp2f((s[r] - hv[j]) - lv[j]);
+                const float e = __builtin_amdgcn_exp2f((s[r] - hv[j]) - lv[j]);
+                const float p = 8 * i + 4 * k.h + j < nv ? e : 0.f;
                 const float ds = p * dp[r];
 #pragma unroll
                 for (int db = 0; db < 2; ++db) {

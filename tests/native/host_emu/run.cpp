@@ -338,10 +338,13 @@ int main(int argc, char** argv) {
     if (argc > 1 && std::strcmp(argv[1], "launchfail") == 0) return run_launchfail();
     if (argc > 1 && std::strcmp(argv[1], "bf16") == 0) return run_bf16(argc, argv);
     if (argc > 1 && std::strcmp(argv[1], "bf16train") == 0) return run_bf16_train(argc, argv);
-    if (argc != 9) {
-        std::fprintf(stderr, "usage: run B heads H W window shift pad_mode outdir\n");
+    if (argc != 9 && argc != 10) {
+        std::fprintf(stderr, "usage: run B heads H W window shift pad_mode outdir [keyinf]\n");
         return 2;
     }
+    // keyinf: the first query channels positive and token 7's key with -inf there, so that every
+    // query's logit for that key is -inf
+    const char* special = argc == 10 ? argv[9] : "";
     const int B = std::atoi(argv[1]), heads = std::atoi(argv[2]), H = std::atoi(argv[3]), W = std::atoi(argv[4]);
     const int k = std::atoi(argv[5]), s = std::atoi(argv[6]), pm = std::atoi(argv[7]);
     const char* dir = argv[8];
@@ -356,6 +359,10 @@ int main(int argc, char** argv) {
     float* dq = alloc_random(B * L * tok, g);
     float* dk = alloc_random(B * rows * tok, g);
     float* dv = alloc_random(B * rows * tok, g);
+    if (std::strcmp(special, "keyinf") == 0) {
+        for (size_t i = 0; i < B * L * heads; ++i) q[64 * i] = std::fabs(q[64 * i]) + 0.1f;
+        for (int h = 0; h < heads; ++h) kk[7 * tok + 64 * h] = -INFINITY;
+    }
     const int hw[2] = {H, W};
     size_t nws = 0;
     if (fla_swin_attn_bwd_workspace(B, heads, 1, hw, k, s, pm, &nws) != 0) return 1;

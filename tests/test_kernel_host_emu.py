@@ -104,6 +104,48 @@ def test_fp32_kernels_on_the_host(emu_binary, tmp_path, case):
         assert np.abs(got - ref).max() <= 2e-5 * m, name
 
 
+def _run_f32(emu_binary, tmp_path, case, special):
+    """One fp32 training problem of one batch entry on the host emulation: name -> fp64 array."""
+    B, heads, H, W, _, _, pm = case
+    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:abort_on_error=1")
+    r = subprocess.run([emu_binary, *map(str, case), str(tmp_path), special], capture_output=True, text=True,
+                       timeout=900, env=env)
+    assert r.returncode == 0 and "ok" in r.stdout, r.stderr[-4000:]
+    rows = {"q": H * W, "dout": H * W, "out": H * W, "dq": H * W, "lse": H * W}
+    res = {}
+    for name in ("q", "k", "v", "dout", "out", "lse", "dq", "dk", "dv"):
+        a = np.fromfile(str(tmp_path / (name + ".f32")), dtype=np.float32).astype(np.float64)
+        res[name] = a.reshape((B, heads, -1) if name == "lse" else (B, rows.get(name, H * W + pm), heads, 64))
+    return res
+
+
+def _one_window_grads(q, k, v, dout):
+    """(dq, dk, dv) of softmax attention over one window, [tokens, heads, 64] in fp64."""
+    z = np.einsum("ihc,jhc->hij", q, k) / 8.0
+    p = np.exp(z - z.max(-1, keepdims=True))
+    p /= p.sum(-1, keepdims=True)
+    o = np.einsum("hij,jhc->ihc", p, v)
+    ds = p * (np.einsum("ihc,jhc->hij", dout, v) - np.einsum("ihc,ihc->hi", dout, o)[:, :, None])
+    return (np.einsum("hij,jhc->ihc", ds, k) / 8.0, np.einsum("hij,ihc->jhc", ds, q) / 8.0,
+            np.einsum("hij,ihc->jhc", p, dout))
+
+
+@pytest.mark.parametrize("hw", [(5, 9), (4, 16), (7, 14)], ids=lambda c: "%dx%d" % c)
+def test_fp32_key_of_minus_infinity_logits_gets_no_gradient(emu_binary, tmp_path, hw):
+    """A key whose logit is -inf for every query: its dk and dv are zero and the other keys'
+    are those of the window without it, also where the last tile of queries is partial (45 and 98
+    tokens; 64 fill their tiles).  dq's first channel is left out: zero weight times the key's -inf."""
+    H, W = hw
+    r = _run_f32(emu_binary, tmp_path, (1, 2, H, W, 16, 0, 0), "keyinf")
+    others = np.arange(H * W) != 7
+    q, k, v, dout = (r[n][0] for n in ("q", "k", "v", "dout"))
+    dq, dk, dv = _one_window_grads(q, k[others], v[others], dout)
+    assert (r["dk"][0, 7] == 0).all() and (r["dv"][0, 7] == 0).all()
+    for name, got, ref in (("dq", r["dq"][0][..., 1:], dq[..., 1:]), ("dk", r["dk"][0, others], dk),
+                           ("dv", r["dv"][0, others], dv)):
+        assert np.abs(got - ref).max() <= 2e-5 * max(1.0, np.abs(ref).max()), name
+
+
 CYCLE_CASES = [  # B, L, d, N, repeats
     (2, 37, 70, 4, 3),     # two chunks (the second of 5 tokens), channels past a multiple of 64
     (1, 200, 64, 32, 3),   # 32 states, seven chunks

@@ -77,3 +77,28 @@ def test_minus_infinity_logits_have_no_weight():
     out = fb.swin_attn(*(t.to("cuda:0") for t in (q, k, v)), 8, 8, 8, 0, 0)
     torch.cuda.synchronize()
     assert (out.cpu().double() - ref).abs().max() <= 1e-5
+
+
+@pytest.mark.parametrize("hw", [(5, 9), (4, 16)], ids=lambda c: "%dx%d" % c)
+def test_key_of_minus_infinity_logits_gets_no_gradient(hw):
+    """A key whose logit is -inf for every query: its dk and dv are zero, and the other keys' and dq
+    (but for the channel where zero weight meets the key's -inf) are those of the window without it,
+    with the last tile of queries partial (45 tokens) and whole."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print("[case] fp32 backward, a key of -inf logits, %dx%d" % hw, flush=True)
+    H, W = hw
+    g = torch.Generator().manual_seed(7)
+    q, k, v, dout = (torch.randn(1, H * W, 2, 64, generator=g) for _ in range(4))
+    q[..., 0] = q[..., 0].abs() + 0.1
+    k[0, 7, :, 0] = -float("inf")
+    gpu = [t.to("cuda:0") for t in (q, k, v, dout)]
+    out, lse = fb.swin_attn_fwd_train(*gpu[:3], [hw], 16, 0, 0)
+    dq, dk, dv = (t.cpu().double() for t in fb.swin_attn_bwd(*gpu[:3], out, gpu[3], lse, [hw], 16, 0, 0))
+    rest = torch.arange(H * W) != 7
+    ref = [t.transpose(1, 2).double().contiguous().requires_grad_() for t in (q, k[:, rest], v[:, rest])]
+    torch.nn.functional.scaled_dot_product_attention(*ref).backward(dout.transpose(1, 2).double().contiguous())
+    rq, rk, rv = (t.grad.transpose(1, 2) for t in ref)
+    assert (dk[0, 7] == 0).all() and (dv[0, 7] == 0).all()
+    for name, got, want in (("dq", dq[..., 1:], rq[..., 1:]), ("dk", dk[:, rest], rk), ("dv", dv[:, rest], rv)):
+        assert (got - want).abs().max() <= 1e-5 * max(1.0, want.abs().max().item()), name
