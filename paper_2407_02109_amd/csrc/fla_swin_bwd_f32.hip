@@ -86,6 +86,12 @@ __device__ __forceinline__ int swz(int r) { return r & 15; }
 // wait until this wave's outstanding global loads (and the LDS writes of its direct loads) are done
 __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8)); }
 
+// the second part of LSE log2(e), lh = LSE kLog2eHi being the first (0 where that is infinite: a
+// query whose LSE the caller sets to +inf has P = 0)
+__device__ __forceinline__ float lse_low(float lse, float lh) {
+    const float ll = __builtin_fmaf(lse, kLog2eLo, __builtin_fmaf(lse, kLog2eHi, -lh));
+    return __builtin_fabsf(lh) < INFINITY ? ll : 0.f;
+}
 __device__ __forceinline__ float dot4(const float4& x, const float4& y, float s) {
     s = __builtin_fmaf(x.x, y.x, s);
     s = __builtin_fmaf(x.y, y.y, s);
@@ -270,7 +276,7 @@ __device__ __forceinline__ void key_role(const SwinBwdArgs& ba, const Block& k, 
             dd += __shfl_xor(dd, 1);
             dd += __shfl_xor(dd, 2);
             const float lh = lse * kLog2eHi;
-            const float ll = __builtin_fmaf(lse, kLog2eLo, __builtin_fmaf(lse, kLog2eHi, -lh));
+            const float ll = lse_low(lse, lh);
             if (pad_here) {
                 zp += __shfl_xor(zp, 1);
                 zp += __shfl_xor(zp, 2);
@@ -397,7 +403,7 @@ __device__ __forceinline__ void query_role(const SwinBwdArgs& ba, const Block& k
     const float lse = __builtin_bit_cast(
         float, __builtin_amdgcn_raw_buffer_load_b32(k.lr, q < k.n ? 4 * k.addr.token(q, (unsigned)k.wr.W) : kOutside, 0, 0));
     const float lh = lse * kLog2eHi;
-    const float ll = __builtin_fmaf(lse, kLog2eLo, __builtin_fmaf(lse, kLog2eHi, -lh));
+    const float ll = lse_low(lse, lh);
     // pad token as key: dS_p = n_pad exp(c <q, k_pad> - LSE) (<dO, v_pad> - D); dq gets dS_p k_pad
     float dsp = 0.f;
     if (has_pad) {

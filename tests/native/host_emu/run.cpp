@@ -339,11 +339,11 @@ int main(int argc, char** argv) {
     if (argc > 1 && std::strcmp(argv[1], "bf16") == 0) return run_bf16(argc, argv);
     if (argc > 1 && std::strcmp(argv[1], "bf16train") == 0) return run_bf16_train(argc, argv);
     if (argc != 9 && argc != 10) {
-        std::fprintf(stderr, "usage: run B heads H W window shift pad_mode outdir [keyinf]\n");
+        std::fprintf(stderr, "usage: run B heads H W window shift pad_mode outdir [keyinf | lseinf]\n");
         return 2;
     }
     // keyinf: the first query channels positive and token 7's key with -inf there, so that every
-    // query's logit for that key is -inf
+    // query's logit for that key is -inf.  lseinf: the backward gets a log-sum-exp of +inf for token 3
     const char* special = argc == 10 ? argv[9] : "";
     const int B = std::atoi(argv[1]), heads = std::atoi(argv[2]), H = std::atoi(argv[3]), W = std::atoi(argv[4]);
     const int k = std::atoi(argv[5]), s = std::atoi(argv[6]), pm = std::atoi(argv[7]);
@@ -373,6 +373,8 @@ int main(int argc, char** argv) {
         std::fprintf(stderr, "forward: %s\n", fla_status_string(rc));
         return 1;
     }
+    if (std::strcmp(special, "lseinf") == 0)
+        for (int h = 0; h < heads; ++h) lse[h * L + 3] = INFINITY;
     emu_kernel_args = 1;
     rc = fla_swin_attn_bwd_f32(q, kk, v, out, dout, lse, dq, dk, dv, ws, nws, B, heads, H, W, 64, k, s, pm, nullptr);
     if (rc != 0) {

@@ -146,6 +146,21 @@ def test_fp32_key_of_minus_infinity_logits_gets_no_gradient(emu_binary, tmp_path
         assert np.abs(got - ref).max() <= 2e-5 * max(1.0, np.abs(ref).max()), name
 
 
+@pytest.mark.parametrize("pm", [0, 1])
+def test_fp32_query_of_infinite_lse_has_no_weight(emu_binary, tmp_path, pm):
+    """A query whose log-sum-exp the caller sets to +inf has P = 0: its dq is zero and the other
+    gradients are those of a zero dout row.  With the pad token (4 x 11 = 44 tokens in a 16 x 16
+    window) that goes for the pad token's P and gradient too."""
+    H, W = 4, 11
+    r = _run_f32(emu_binary, tmp_path, (1, 2, H, W, 16, 0, pm), "lseinf")
+    q, k, v, dout = (r[n] for n in ("q", "k", "v", "dout"))
+    dout[0, 3] = 0
+    refs = O.swin_attention_bwd(q, k, v, dout, H, W, 16, 0, pm)
+    assert (r["dq"][0, 3] == 0).all()
+    for name, ref in zip(("dq", "dk", "dv"), refs):
+        assert np.abs(r[name] - ref).max() <= 2e-5 * max(1.0, np.abs(ref).max()), name
+
+
 CYCLE_CASES = [  # B, L, d, N, repeats
     (2, 37, 70, 4, 3),     # two chunks (the second of 5 tokens), channels past a multiple of 64
     (1, 200, 64, 32, 3),   # 32 states, seven chunks

@@ -102,3 +102,24 @@ def test_key_of_minus_infinity_logits_gets_no_gradient(hw):
     assert (dk[0, 7] == 0).all() and (dv[0, 7] == 0).all()
     for name, got, want in (("dq", dq[..., 1:], rq[..., 1:]), ("dk", dk[:, rest], rk), ("dv", dv[:, rest], rv)):
         assert (got - want).abs().max() <= 1e-5 * max(1.0, want.abs().max().item()), name
+
+
+@pytest.mark.parametrize("pm", [0, 1])
+def test_query_of_infinite_lse_has_no_weight(pm):
+    """A query whose log-sum-exp the caller sets to +inf has P = 0: its dq is zero, and the other
+    gradients (the pad token's too) are those of a zero dout row."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print("[case] fp32 backward, infinite log-sum-exp, pad mode %d" % pm, flush=True)
+    wl = synth.Workload("case", 1, 2, 4, 11, 64, 16, 0, "f32", seed=79, pad_mode=pm)
+    q, k, v = synth.make_inputs(wl)
+    dout = synth.make_grad(wl)
+    gpu = [t.to("cuda:0") for t in (q, k, v, dout)]
+    out, lse = fb.swin_attn_fwd_train(*gpu[:3], [(4, 11)], 16, 0, pm)
+    lse[:, :, 3] = float("inf")
+    grads = fb.swin_attn_bwd(*gpu[:3], out, gpu[3], lse, [(4, 11)], 16, 0, pm)
+    dout[:, 3] = 0
+    f64 = [synth.to_f64_numpy(t) for t in (q, k, v, dout)]
+    assert (synth.to_f64_numpy(grads[0])[:, 3] == 0).all()
+    for name, got, ref in zip(("dq", "dk", "dv"), grads, O.swin_attention_bwd(*f64, 4, 11, 16, 0, pm)):
+        assert np.abs(synth.to_f64_numpy(got) - ref).max() <= 1e-5 * max(1.0, np.abs(ref).max()), name
