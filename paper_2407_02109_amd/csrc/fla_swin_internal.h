@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 namespace fla {
@@ -60,7 +61,6 @@ struct SwinArgs {
     int window, shift;
     int origin;                 // (window - shift) % window: virtual tokens in front of each axis
     int nqb;                    // query blocks per window: ceil(max window size / kQueryBlock)
-    int n_max;                  // tokens of the largest window
     int pad_mode;               // 0 = mask virtual keys, 1 = pad token at row L
     int64_t L;                  // tokens per batch entry, all grids (the pad token's row)
     int64_t tok_stride;         // elements between consecutive tokens: heads * head_dim
@@ -84,7 +84,13 @@ struct SwinArgs {
     float rope_rev[kHeadDim / 4];
     double rope_freq[kHeadDim / 4];
     int head_dim;               // channels per head (the forward kernels' instance)
+    int n_max;                  // tokens of the largest window (read by the launchers only)
 };
+// B .. pad_mode are one 32-byte argument load of the workgroup decode: with n_max between nqb and
+// pad_mode it took three, with a wait before the decode (bf16 forward, 12 heads, 64x64 tokens, window
+// 16: 9.22 -> 9.36 us).  New members go to the end.
+static_assert(offsetof(SwinArgs, pad_mode) == offsetof(SwinArgs, B) + 6 * sizeof(int) &&
+              offsetof(SwinArgs, L) == offsetof(SwinArgs, B) + 8 * sizeof(int), "the decode's argument load");
 
 
 // Workgroups of a bf16 forward launch: one per unit in groups of 8 (the last one padded), or
