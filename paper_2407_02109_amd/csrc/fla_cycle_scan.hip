@@ -125,9 +125,12 @@ __device__ __forceinline__ void add_shares(float (*red)[kTokens][64], int wave, 
     }
 }
 
-template <int N, int SPLIT>
+// EARLY (one wave per group): every token's y is stored at once instead of with its group's, which takes
+// 76 registers instead of 96 at 16 states, six waves per SIMD instead of five.
+template <int N, int SPLIT, bool EARLY>
 __global__ __launch_bounds__(64 * SPLIT) __attribute__((amdgpu_waves_per_eu(1, SPLIT >= 4 ? 6 : 8)))
 void cycle_scan_chunks(CycleArgs c) {
+    static_assert(!EARLY || SPLIT == 1, "the shares of y are added first");
     using W = ScanWave<N, SPLIT>;
     constexpr int NW = W::NW, PER = W::PER, PAIR = W::PAIR;
     __shared__ float red[2][SPLIT][kTokens][64];
@@ -178,9 +181,11 @@ void cycle_scan_chunks(CycleArgs c) {
                     y2[n & 1] = __builtin_fmaf(cv[p][n] * ia[n], g[n], y2[n & 1]);
                 }
                 acc[j] = y2[0] + y2[1];
+                if constexpr (EARLY) w.store(c, c.y, tg + j, acc[j]);
                 sd += dl[j];
             }
         }
+        if constexpr (EARLY) return;
         add_shares<SPLIT, PER>(red[buf], w.wave, w.lane, acc);
         buf ^= 1;
 #pragma unroll
@@ -342,7 +347,8 @@ void cycle_scan_outputs(CycleArgs c) {
     });
 }
 
-template <int N, int SPA, int SPC>
+// SPA, SPC: waves per group of passes A and C
+template <int N, int SPA, int SPC, bool EARLY = false>
 hipError_t launch_n(const CycleArgs& a, hipStream_t stream) {
     CycleArgs args = a;
     // carry pass: up to 8 segments of at least kBatch chunks per (channel, state)
@@ -350,7 +356,7 @@ hipError_t launch_n(const CycleArgs& a, hipStream_t stream) {
     while (args.seg < 8 && (long long)args.seg * kBatch < a.nch) args.seg *= 2;
     void* params[] = {&args};
     const long long scan_groups = (long long)a.B * a.nch * a.cgroups;
-    hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(&cycle_scan_chunks<N, SPA>),
+    hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(&cycle_scan_chunks<N, SPA, EARLY>),
                                    dim3((unsigned)scan_groups), dim3(64 * SPA), params, 0, stream);
     if (e != hipSuccess) return e;
     const long long per_wg = 256 / args.seg;
@@ -367,14 +373,21 @@ hipError_t launch_n(const CycleArgs& a, hipStream_t stream) {
 bool cycle_states_supported(int N) { return N == 1 || N == 2 || N == 4 || N == 8 || N == 16 || N == 32; }
 
 hipError_t launch_cycle_scan(const CycleArgs& a, hipStream_t stream) {
-    // Waves that share one chunk's states, by the number of (chunk, 64 channels) groups.  Few groups
-    // leave SIMDs without a wave (one wave alone issues at half the rate of two): more waves per
-    // group.  Many: fewer, since every wave reads the group's x and Delta and joins the sum.
-    // Measured per call, 768 channels, us, split 1 / 2 / 4 / 8: 32 states, 4096 tokens (768 groups)
-    // 107 / 100 / 73 / 72; 32768 tokens (1536) 502 / 499 / 371 / 444; 65536 tokens (3072) 697 / 809 /
-    // 679 / 873, and 661 with pass A at 4 and pass C at 1.  16 states: 65536 tokens 454 / 422 / 470 /
-    // 649; 20000 tokens of 384 channels (474) 222 / 228 / 151 / 148; 2 x 65536 of 1024 (8192) 930 /
-    // 999 / 1166 / 1607.  Up to 8 states one wave holds them all.
+    // Waves that share one chunk's states, by the number of (chunk, 64 channels) groups; the numbers are
+    // those of 256 compute units, 1024 SIMDs.  Few groups leave SIMDs without a wave (one wave alone
+    // issues at half the rate of two): more waves per group, as long as six per SIMD hold them all
+    // (1536 groups of four waves).  Many: fewer, since every wave reads the group's x and Delta and joins
+    // the sum.  Up to 8 states one wave holds them all.  Measured per call, us, by waves in pass A / C
+    // (chunks of 256 tokens unless said; "early": see cycle_scan_chunks):
+    //   32 states  8/8 and 4/4: 768 groups (chunks of 64) 72, 73.  4/4 and 4/1: 1536 groups 375, 406;
+    //     1884 476, 531; 2160 541, 561; 2448 585, 596; 2820 634, 633; 3060 676, 662; 3072 681, 666; 3288 733,
+    //     787; 4104 871, 881; 4608 979, 997; 5640 1163, 1187; 6144 1255, 1245; 8192 1653, 1630.  1/1 is slower
+    //     throughout (3072: 718).
+    //   16 states  4/4, 2/1, 1/1: 948 groups 188, 231, 237; 1416 240, 246, 273; 1536 248, 268, 287; 1548 306, 269,
+    //     287; 1884 352, 329, 312; 2160 393, 336, 366; 2448 418, 362, 380; 2820 452, 380, 392; 3060 469, 405, 400;
+    //     3288 554, 473, 459; 4608 700, 579, 552.  2/2 lies between 2/1 and 4/4 up to 3060 groups and is slower
+    //     than 2/1 from there (4608: 682).  1/1 and 1/1 early: 4608 groups 552, 554; 5640 679, 637; 6144 716, 662,
+    //     in chunks of 64 194, 181; 8192 897, 922: early where six waves per SIMD hold all groups and five do not.
     const long long groups = (long long)a.B * a.nch * a.cgroups;
     switch (a.N) {
         case 1: return launch_n<1, 1, 1>(a, stream);
@@ -382,11 +395,12 @@ hipError_t launch_cycle_scan(const CycleArgs& a, hipStream_t stream) {
         case 4: return launch_n<4, 1, 1>(a, stream);
         case 8: return launch_n<8, 1, 1>(a, stream);
         case 16:
-            return groups >= 6144   ? launch_n<16, 1, 1>(a, stream)
-                   : groups >= 2048 ? launch_n<16, 2, 2>(a, stream)
-                                    : launch_n<16, 4, 4>(a, stream);
+            return groups <= 1536                     ? launch_n<16, 4, 4>(a, stream)
+                   : groups <= 3072                   ? launch_n<16, 2, 1>(a, stream)
+                   : groups > 5120 && groups <= 6144 ? launch_n<16, 1, 1, true>(a, stream)
+                                                      : launch_n<16, 1, 1>(a, stream);
         case 32:
-            return groups >= 3072   ? launch_n<32, 4, 1>(a, stream)
+            return groups >= 2816   ? launch_n<32, 4, 1>(a, stream)
                    : groups >= 1024 ? launch_n<32, 4, 4>(a, stream)
                                     : launch_n<32, 8, 8>(a, stream);
         default: return hipErrorInvalidValue;

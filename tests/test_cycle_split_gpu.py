@@ -13,8 +13,11 @@ from paper_2407_02109_amd import binding as fb, synth
 pytestmark = pytest.mark.gpu
 
 CASES = [  # B, L, d, N
-    (1023, 5, 1, 32), (1024, 6, 3, 32), (3071, 7, 2, 32), (3072, 5, 3, 32),     # 8 | 4 | 4 | 4 and 1 waves
-    (2047, 3, 2, 16), (2048, 7, 1, 16), (6143, 6, 2, 16), (6144, 5, 1, 16),     # 4 | 2 | 2 | 1 waves
+    # waves per group in pass A / C: 8/8 | 4/4, 4/4 | 4/1
+    (1023, 5, 1, 32), (1024, 6, 3, 32), (2815, 7, 2, 32), (2816, 5, 1, 32), (3071, 7, 2, 32), (3072, 5, 3, 32),
+    # 4/4 | 2/1, 2/1 | 1/1, 1/1 | 1/1 early, early | 1/1
+    (1536, 5, 1, 16), (1537, 6, 2, 16), (2047, 3, 2, 16), (2048, 7, 1, 16), (3072, 6, 2, 16), (3073, 7, 3, 16),
+    (5120, 5, 2, 16), (5121, 7, 1, 16), (6143, 6, 2, 16), (6144, 5, 1, 16), (6145, 7, 2, 16), (2561, 35, 66, 16),
     (3072, 35, 65, 32), (40, 35, 65, 32),   # two chunks, two channel groups
     (64, 9, 70, 8), (64, 9, 70, 4),
 ]
