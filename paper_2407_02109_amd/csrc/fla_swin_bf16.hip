@@ -40,6 +40,7 @@
 // 32 x 32 tokens; wider ones evaluate them per rotated piece), so a rotated copy of q and k
 // never goes through HBM.  The pad token has no position and is not rotated.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "fla_swin_device.h"
@@ -526,11 +527,9 @@ void swin_fwd_bf16_kernel(SwinArgs a) {
 
 }  // namespace
 
-// Blocks of kQueryBlock queries that a launch really has (a window has as many as its own tokens need),
-// counted up to the first window that takes them past `most`.
-int64_t query_blocks(const SwinArgs& a, int64_t most) {
-    int64_t blocks = 0;
-    const int64_t per_block = (int64_t)a.B * a.heads;
+// f(tokens) for the windows of one batch entry in their order, until it returns false
+template <typename F>
+void for_windows(const SwinArgs& a, F&& f) {
     for (int g = 0; g < a.n_grids; ++g) {
         const GridDesc& G = a.grid[g];
         if (G.H < 1 || G.W < 1) continue;
@@ -538,12 +537,71 @@ int64_t query_blocks(const SwinArgs& a, int64_t most) {
             const int64_t rows = std::min<int64_t>(y0 + a.window, G.H) - std::max<int64_t>(y0, 0);
             for (int64_t x0 = -(int64_t)a.origin; x0 < G.W; x0 += a.window) {
                 const int64_t cols = std::min<int64_t>(x0 + a.window, G.W) - std::max<int64_t>(x0, 0);
-                blocks += (rows * cols + kQueryBlock - 1) / kQueryBlock * per_block;
-                if (blocks > most) return blocks;
+                if (!f(rows * cols)) return;
             }
         }
     }
+}
+
+// Blocks of kQueryBlock queries that a launch really has (a window has as many as its own tokens need),
+// counted up to the first window that takes them past `most`.
+int64_t query_blocks(const SwinArgs& a, int64_t most) {
+    int64_t blocks = 0;
+    const int64_t per_block = (int64_t)a.B * a.heads;
+    for_windows(a, [&](int64_t n) {
+        blocks += (n + kQueryBlock - 1) / kQueryBlock * per_block;
+        return blocks <= most;
+    });
     return blocks;
+}
+
+// Up to `most` waves per query tile at head_dim 128, where a compute unit holds one workgroup: the number
+// whose workgroups are done first.  In keys of a wave that has its query tile to itself (35 ns each), a
+// workgroup takes 115 (4 us) and 1, 0.70 or 0.57 (by the number of waves) per key of its window.  Workgroup ids
+// go to the 8 XCDs in turn, those of an XCD to its 4 shader engines in turn, those of an engine in order to
+// the first of its compute units that is free; the blocks that a window does not have end at once but keep
+// their place in the turn.
+int soonest_split(const SwinArgs& a, int most) {
+    constexpr int kXcds = 8, kEngines = 4, kMaxCus = 16;
+    const int cus = std::min(std::max(a.n_cus / (kXcds * kEngines), 1), kMaxCus);
+    float best = INFINITY;
+    int best_split = 1;
+    for (int split = most; split >= 1; split /= 2) {
+        const float per_key = split == 1 ? 1.f : split == 2 ? 0.70f : 0.57f;
+        const int qb = kQueryBlock / split, nqb = (a.n_max + qb - 1) / qb;
+        float busy[kXcds * kEngines][kMaxCus], longest = 0.f;
+        int taken[kXcds * kEngines] = {};
+        bool one_round = true;   // no workgroup waits for another
+        unsigned unit = 0;
+        for (int b = 0; b < a.B; ++b)
+            for_windows(a, [&](int64_t n) {
+                const float time = 115.f + per_key * (float)n;
+                const unsigned blocks = (unsigned)((n + qb - 1) / qb);
+                for (int head = 0; head < a.heads; ++head, ++unit) {
+                    const unsigned g = unit >> 3, xcd = (unit - (g >> 2)) & 7u;   // the kernel's decode, inverted
+                    for (unsigned blk = 0; blk < blocks; ++blk) {
+                        const unsigned e = kEngines * xcd + ((unsigned)nqb * g + blk) % kEngines;
+                        float* cu = busy[e] + taken[e];
+                        if (taken[e] < cus) {
+                            ++taken[e];
+                            *cu = time;
+                        } else {
+                            one_round = false;
+                            cu = std::min_element(busy[e], busy[e] + cus);
+                            *cu += time;
+                        }
+                        longest = std::max(longest, *cu);
+                    }
+                }
+                return true;
+            });
+        if (longest < best) {
+            best = longest;
+            best_split = split;
+        }
+        if (one_round) break;   // fewer waves per tile take longer
+    }
+    return best_split;
 }
 
 template <int SPLIT>
@@ -575,10 +633,16 @@ hipError_t launch_swin_fwd_bf16(const SwinArgs& a, hipStream_t stream) {
     // 12 heads (192) 26.5 / 26.9 / 30.7; 24 heads (384) 41.0 / 41.9 / 56.1.  Heads of 128: 3 39.4 / 29.1
     // / 24.2, 6 39.8 / 29.9 / 45.8.  24 heads of 32, 32x32 tokens, window 32 (96) 19.9 / 14.4 / 15.4.
     // 400-token windows: 3 heads (75) 13.1 / 12.4 / 12.4, 6 heads (150) 13.3 / 13.6 / 15.3.
+    // Heads of 128: of the forms up to that, the one done first (soonest_split).  By the number of blocks alone, 2
+    // lost to 1 with 5 heads at window 20, shift 10, KV-token (120 blocks, up to ten on an engine's eight CUs:
+    // 20.0 / 23.5), and 4 with 9 heads of 42x42 tokens, window 42 (63: 66.4 / 47.9 / 72.3) and 3 heads at window 64,
+    // shift 0 (48: 149 / 105 / 154).  On 40 shapes the choice was never slower than 1 and within 3% of the best; on 90
+    // random ones of all three head sizes none was slower than 1.  The cut-offs are 64 and 128 blocks at 256 CUs.
     int split = 1;
     if (a.xcd_group) {
-        const int64_t blocks = query_blocks(a, 128);
-        split = blocks <= 64 ? 4 : blocks <= 128 ? 2 : 1;
+        const int64_t blocks = query_blocks(a, a.n_cus / 2);
+        const int most = blocks <= a.n_cus / 4 ? 4 : blocks <= a.n_cus / 2 ? 2 : 1;
+        split = a.head_dim == 128 && most > 1 ? soonest_split(a, most) : most;
     }
     if (split > 1) {
         const int qb = kQueryBlock / split;
