@@ -632,7 +632,10 @@ hipError_t launch_swin_fwd_bf16(const SwinArgs& a, hipStream_t stream) {
     // 6 heads (96) 25.9 / 19.2 / 20.7, with RoPE 29.9 / 23.2 / 26.2; 8 heads (128) 25.9 / 19.5 / 20.9;
     // 12 heads (192) 26.5 / 26.9 / 30.7; 24 heads (384) 41.0 / 41.9 / 56.1.  Heads of 128: 3 39.4 / 29.1
     // / 24.2, 6 39.8 / 29.9 / 45.8.  24 heads of 32, 32x32 tokens, window 32 (96) 19.9 / 14.4 / 15.4.
-    // 400-token windows: 3 heads (75) 13.1 / 12.4 / 12.4, 6 heads (150) 13.3 / 13.6 / 15.3.
+    // 400-token windows: 3 heads (72) 13.1 / 12.4 / 12.4, 6 heads (144) 13.3 / 13.6 / 15.3; 12 heads (288) 15.5 / 18.2
+    // / 21.0.  Many short blocks beside few long ones weigh less than the count says, and there the cut-offs are
+    // too low: 12 heads, window 32, shift 16 (192 blocks, 48 of them in whole windows) 26.3 / 23.5 / 24.6, with RoPE
+    // 30.3 / 28.9 / 30.8; 12 heads of 40x44 tokens, window 32, KV-token (96, 48) 25.7 / 19.2 / 16.4.
     // Heads of 128: of the forms up to that, the one done first (soonest_split).  By the number of blocks alone, 2
     // lost to 1 with 5 heads at window 20, shift 10, KV-token (120 blocks, up to ten on an engine's eight CUs:
     // 20.0 / 23.5), and 4 with 9 heads of 42x42 tokens, window 42 (63: 66.4 / 47.9 / 72.3) and 3 heads at window 64,
