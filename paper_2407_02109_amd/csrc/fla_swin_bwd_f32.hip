@@ -53,7 +53,6 @@ constexpr int TB = 2 * TL;             // tokens per block: two waves per tile
 constexpr int CH = 2 * TL;             // streamed rows per chunk: one tile per sh
 constexpr int ROWP = D / 4;            // 16-byte pieces per row
 constexpr int BUF = CH * D;            // floats of one chunk's rows of one tensor
-constexpr unsigned kGridX = 1u << 22;  // workgroups per row of the launch grid
 // log2(e) in two parts: LSE log2(e) is kept as a pair, so that P carries the rounding of the
 // stored LSE and not that of a product of its size as well
 constexpr float kLog2eHi = 1.44269502f, kLog2eLo = 1.92596303e-8f;

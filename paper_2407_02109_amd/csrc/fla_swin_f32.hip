@@ -45,7 +45,6 @@ constexpr int TL = 32;                 // queries (keys) per tile
 constexpr int QB = 2 * TL;             // queries per workgroup: two waves per tile
 constexpr int KC = 2 * TL;             // keys per LDS chunk: one tile per kh
 constexpr int kRopeTab = 32;           // window rows / columns covered by the RoPE table
-constexpr unsigned kGridX = 1u << 22;  // workgroups per row of the launch grid
 
 constexpr float kLn2Hi = 0.693147182f, kLn2Lo = -1.90465430e-9f;
 

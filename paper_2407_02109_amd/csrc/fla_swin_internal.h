@@ -38,6 +38,14 @@ __host__ __device__ constexpr bool fwd_head_dim_ok(int d) { return d == 32 || d 
 constexpr int kQueryBlock = 256; // queries of one window handled by one bf16 forward workgroup
 constexpr int kBwdBlock = 128;   // tokens of one backward block
 
+// Workgroups per row of an fp32 launch grid (a multiple of 8): ids past one row go on along y.  The host
+// build of the tests sets a small one, so that ordinary problems take several rows.
+#ifndef FLA_GRID_X
+#define FLA_GRID_X (1u << 22)
+#endif
+constexpr unsigned kGridX = FLA_GRID_X;
+static_assert(kGridX % 8 == 0, "a row ends with a whole group of ids");
+
 constexpr int kMaxGrids = 8;    // token grids of one multi-scale sequence
 
 // One token grid of the sequence (a single grid, or the image grid and the anchor-map grid

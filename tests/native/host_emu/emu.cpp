@@ -48,13 +48,14 @@ hipError_t hipLaunchKernel(const void* fn, dim3 grid, dim3 block, void** args, s
     g_wave_barriers.clear();
     for (unsigned w = 0; w < nw; ++w)
         g_wave_barriers.emplace_back(std::make_unique<std::barrier<>>((std::ptrdiff_t)std::min(64u, block.x - 64 * w)));
-    for (unsigned b = 0; b < grid.x; ++b) {
+    if (grid.z != 1 || block.y != 1 || block.z != 1) return hipErrorInvalidValue;   // (no kernel has them)
+    for (unsigned b = 0; b < grid.x * grid.y; ++b) {
         std::vector<std::thread> threads;
         threads.reserve(block.x);
         for (unsigned t = 0; t < block.x; ++t)
             threads.emplace_back([=]() {
                 threadIdx = {t, 0, 0};
-                blockIdx = {b, 0, 0};
+                blockIdx = {b % grid.x, b / grid.x, 0};
                 if (emu_kernel_args == 0)
                     reinterpret_cast<void (*)(fla::SwinArgs)>(const_cast<void*>(fn))(*static_cast<fla::SwinArgs*>(args[0]));
                 else if (emu_kernel_args == 1)
