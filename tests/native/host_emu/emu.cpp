@@ -1,6 +1,7 @@
 // The launch emulation behind hip_runtime.h (see there), with the wave-level exchange that the
 // matrix-core and cross-lane builtins of amdgcn_host.h use, and a device that reports gfx950.
 #include <barrier>
+#include <cstdlib>
 #include <memory>
 #include <thread>
 #include <vector>
@@ -27,7 +28,9 @@ hipError_t hipGetDevice(int* device) {
 }
 hipError_t hipGetDeviceProperties(hipDeviceProp_t* prop, int) {
     std::strcpy(prop->gcnArchName, "gfx950:sramecc+:xnack-");
-    prop->multiProcessorCount = 256;
+    // EMU_CUS: a device of that many compute units, so that small launches take the forms of large ones
+    const char* cus = std::getenv("EMU_CUS");
+    prop->multiProcessorCount = cus ? std::atoi(cus) : 256;
     return hipSuccess;
 }
 hipError_t hipGetLastError() { return hipSuccess; }

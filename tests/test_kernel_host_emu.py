@@ -226,8 +226,32 @@ def test_bf16_forward_on_the_host(emu_binary, tmp_path, case):
     and the ballot emulated per wave) and the device header, built for the host with
     AddressSanitizer and UndefinedBehaviorSanitizer on exact-size buffers, against the fp64
     oracle at the GPU tests' bf16 bounds (max 2e-2, mean 2e-3)."""
+    _bf16_forward(emu_binary, tmp_path, case, 256)
+
+
+SPLIT_CASES = [  # compute units of the emulated device (more than cus / 2 blocks of 256 queries: one wave per
+    # query tile, more than cus / 4: two), then as above; windows of 289 and 324 tokens and smaller ones
+    (2, "plain", 1, 1, "17x17", 17, 0, 0, 64, 0, 0),
+    (4, "plain", 1, 1, "17x17", 17, 0, 0, 64, 0, 0),
+    (2, "plain", 1, 1, "17x19", 18, 0, 1, 32, 0, 0),
+    (4, "plain", 1, 1, "17x17", 18, 0, 1, 128, 0, 0),
+    (2, "rope", 1, 1, "18x18", 18, 0, 0, 64, 100.0, 0.5),
+    (4, "rope", 1, 1, "18x18", 18, 0, 0, 64, 100.0, 0.5),
+    (6, "ms", 1, 1, "17x17,5x9", 18, 0, 1, 64, 0, 0),
+    (8, "ms", 1, 1, "17x17,5x9", 18, 0, 1, 128, 0, 0),
+]
+
+
+@pytest.mark.parametrize("case", SPLIT_CASES, ids=lambda c: "-".join(map(str, c)).replace(",", "+"))
+def test_bf16_forward_by_waves_per_tile_on_the_host(emu_binary, tmp_path, case):
+    """Windows of more than 256 tokens with one and two waves per query tile (the cases above
+    have four)."""
+    _bf16_forward(emu_binary, tmp_path, case[1:], case[0])
+
+
+def _bf16_forward(emu_binary, tmp_path, case, cus):
     kind, B, heads, grids, k, s, pm, d, theta, scale = case
-    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:abort_on_error=1")
+    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:abort_on_error=1", EMU_CUS=str(cus))
     r = subprocess.run([emu_binary, "bf16", kind, str(B), str(heads), grids, str(k), str(s), str(pm), str(d),
                         str(theta), str(scale), str(tmp_path)], capture_output=True, text=True, timeout=900, env=env)
     assert r.returncode == 0 and "ok" in r.stdout, r.stderr[-4000:]
