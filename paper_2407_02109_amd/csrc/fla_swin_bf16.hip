@@ -188,7 +188,7 @@ constexpr int kRopeTab = 32;   // window rows / columns covered by the per-workg
 template <bool MULTI, bool ROPE, int D, int SPLIT>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(Cfg<D>::WAVES, Cfg<D>::WAVES)))
 void swin_fwd_bf16_kernel(SwinArgs a) {
-    static_assert(!ROPE || D == kHeadDim, "RoPE: head_dim 64 only");
+    static_assert(!ROPE || (D == kHeadDim && !MULTI), "RoPE: one grid of head_dim 64 only");
     constexpr int KS = Cfg<D>::KS, TPR = Cfg<D>::TPR, TPR_LOG = Cfg<D>::TPR_LOG, RPP = Cfg<D>::RPP;
     constexpr int NQT = THREADS / 64 / SPLIT;   // query tiles per workgroup
     __shared__ __attribute__((aligned(16))) uint16_t Ks[KC * KS];
@@ -525,8 +525,6 @@ void swin_fwd_bf16_kernel(SwinArgs a) {
     }
 }
 
-}  // namespace
-
 // f(tokens) for the windows of one batch entry in their order, until it returns false
 template <typename F>
 void for_windows(const SwinArgs& a, F&& f) {
@@ -612,13 +610,14 @@ const void* kernel(const SwinArgs& a) {
         return multi ? reinterpret_cast<const void*>(&swin_fwd_bf16_kernel<true, false, D, SPLIT>)
                      : reinterpret_cast<const void*>(&swin_fwd_bf16_kernel<false, false, D, SPLIT>);
     };
-    if (a.rope)   // head_dim 64 only (the host checks)
-        return multi ? reinterpret_cast<const void*>(&swin_fwd_bf16_kernel<true, true, kHeadDim, SPLIT>)
-                     : reinterpret_cast<const void*>(&swin_fwd_bf16_kernel<false, true, kHeadDim, SPLIT>);
+    if (a.rope)   // one grid of head_dim 64 only (the host checks)
+        return reinterpret_cast<const void*>(&swin_fwd_bf16_kernel<false, true, kHeadDim, SPLIT>);
     return a.head_dim == 32    ? plain(std::integral_constant<int, 32>{})
            : a.head_dim == 128 ? plain(std::integral_constant<int, 128>{})
                                : plain(std::integral_constant<int, kHeadDim>{});
 }
+
+}  // namespace
 
 hipError_t launch_swin_fwd_bf16(const SwinArgs& a, hipStream_t stream) {
     SwinArgs args = a;

@@ -133,19 +133,6 @@ inline emu_floatx16 __builtin_amdgcn_mfma_f32_32x32x2f32(float a, float b, emu_f
     return d;
 }
 
-// 16 outer products of 4 x 1 and 1 x 4, D = A B + C: lane l supplies row l % 4 of A and column l % 4
-// of B of block l / 4 and receives that column of D, row r in element r.
-typedef float emu_floatx4 __attribute__((ext_vector_type(4)));
-inline emu_floatx4 __builtin_amdgcn_mfma_f32_4x4x1f32(float a, float b, emu_floatx4 c, int, int, int) {
-    float* s = reinterpret_cast<float*>(emu_wave_slots());
-    const unsigned l = emu_lane_id();
-    s[l] = a;
-    emu_wave_barrier();
-    emu_floatx4 d = c;
-    for (int r = 0; r < 4; ++r) d[r] = std::fma(s[(l & ~3u) + r], b, d[r]);
-    return d;
-}
-
 // Swaps the upper 32 lanes of the first operand with the lower 32 lanes of the second:
 // returns (new first, new second).
 inline emu_u32x2 __builtin_amdgcn_permlane32_swap(unsigned x, unsigned y, bool, bool) {
