@@ -29,6 +29,14 @@
  * owned by the caller; the library never allocates, frees, copies or synchronises.
  * q, k and v may alias each other; out must not overlap any of them.
  *
+ * Reproducibility.  The same call on the same device gives the same bits every time.  The bits of one
+ * image and head may differ between calls of different size, within the rounding of the data type:
+ * the bf16 forwards share the keys of windows of more than 256 tokens among one, two or four waves by
+ * the size of the whole launch (B, heads and every grid), and add their parts in that order; the bf16
+ * backward takes one of two kernels by the largest window of the launch; Cycle-scan with 16 or 32
+ * states sums its output in an order that depends on B, L and d.  The fp32 forward and backward give
+ * an image and head the same bits alone and in a batch.
+ *
  * Errors.  Each entry point checks its arguments in this order and returns the first
  * failure without launching anything and without touching any output: FLA_ERR_SHAPE
  * (n_grids, then negative sizes), FLA_ERR_NULL, FLA_ERR_ALIGN, FLA_ERR_HEAD_DIM,

@@ -123,3 +123,18 @@ def test_query_of_infinite_lse_has_no_weight(pm):
     assert (synth.to_f64_numpy(grads[0])[:, 3] == 0).all()
     for name, got, ref in zip(("dq", "dk", "dv"), grads, O.swin_attention_bwd(*f64, 4, 11, 16, 0, pm)):
         assert np.abs(synth.to_f64_numpy(got) - ref).max() <= 1e-5 * max(1.0, np.abs(ref).max()), name
+
+
+def test_an_image_has_the_same_bits_alone_and_in_a_batch():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print("[case] fp32 alone and in a batch", flush=True)
+    wl = synth.Workload("case", 3, 2, 21, 19, 64, 18, 5, "f32", seed=80, pad_mode=1)
+    q, k, v = (t.to("cuda:0") for t in synth.make_inputs(wl))
+    dout = synth.make_grad(wl).to("cuda:0")
+    both = []
+    for b in (slice(0, 3), slice(2, 3)):
+        t = [x[b].contiguous() for x in (q, k, v, dout)]
+        out, lse = fb.swin_attn_fwd_train(*t[:3], [(21, 19)], 18, 5, 1)
+        both.append([x[-1] for x in (out, lse, *fb.swin_attn_bwd(*t[:3], out, t[3], lse, [(21, 19)], 18, 5, 1))])
+    assert all(torch.equal(x, y) for x, y in zip(*both))
