@@ -219,8 +219,8 @@ int fla_swin_attn_ms_fwd_lse_f32(const float* q, const float* k, const float* v,
 /* Workspace the backward needs, in bytes (host arithmetic only): in FLA_PAD_KVTOKEN mode 512
  * bytes per (batch entry, head, window, block), each block's share of the pad token's
  * gradient, where the blocks are the 128-token pieces of the largest window (nbb =
- * ceil(max window tokens / 128)); 0 in FLA_PAD_MASK mode.  The fp32 entry points need at most
- * as much.  Single-grid callers pass n_grids = 1 and grid_hw = {Hgrid, Wgrid}.  Argument
+ * ceil(max window tokens / 128)); 0 in FLA_PAD_MASK mode.  The fp32 entry points take the same
+ * size and use one share per window of it.  Single-grid callers pass n_grids = 1 and grid_hw = {Hgrid, Wgrid}.  Argument
  * errors as for the forward; bytes must be non-NULL (FLA_ERR_NULL). */
 int fla_swin_attn_bwd_workspace(int B, int heads, int n_grids, const int* grid_hw, int window,
                                 int shift, int pad_mode, size_t* bytes);

@@ -283,8 +283,9 @@ int forward(const void* q, const void* k, const void* v, void* out, float* lse, 
 }
 
 // Workspace bytes of a backward call: one pad-gradient partial per (b, head, window, block)
-// in KV-token mode, with the bf16 kernel's blocks of kBwdBlock tokens (at least as many as
-// the fp32 kernels' blocks).  Assumes the geometry is valid.
+// in KV-token mode, with the bf16 kernel's blocks of kBwdBlock tokens.  The fp32 kernel writes one
+// partial per window and shares this size, since the query does not know the data type.  Assumes the
+// geometry is valid.
 int64_t workspace_bytes(int B, int heads, const Geometry& geo, int pad_mode) {
     if (pad_mode != FLA_PAD_KVTOKEN) return 0;
     return int64_t(B) * heads * geo.n_windows * geo.nbb * fla::kPadPartial * 4;

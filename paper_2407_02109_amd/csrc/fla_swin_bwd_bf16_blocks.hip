@@ -90,7 +90,6 @@ static_assert(THREADS == 2 * kPadPartial, "two threads per pad-gradient channel"
 
 typedef short shortx4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) shortx4 lds_shortx4;
-typedef __attribute__((address_space(3))) void lds_void;
 
 // bf16 index of channel c of row r in a swizzled LDS row array: 16-byte piece p of row r
 // holds channels 8 (p ^ f(r)) .. + 7, f(r) = (r >> 1) & 7, so the 16 rows a 16-lane read of
@@ -118,9 +117,6 @@ __device__ __forceinline__ TileOff tile_offsets(int lane) {
     o.t = row * ROW + (((2 * g1 + (q >> 1)) ^ swz(row)) << 3) + 4 * (q & 1);
     return o;
 }
-
-// wait until this wave's outstanding global loads (and the LDS writes of its direct loads) are done
-__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8)); }
 
 // Rows 16 w .. 16 w + 15 of a chunk (chunk-local row r = window-local token base + r, present
 // when r < nrows, zero otherwise) from a buffer resource straight into the swizzled LDS

@@ -76,14 +76,9 @@ static_assert(2 * 4 * NW * 64 * 4 <= OFF_ROWS && OFF_ROWS + 2 * TB * D <= OFF_LH
 static_assert(2 * LDS * 4 <= 160 * 1024, "two workgroups per compute unit");
 static_assert(THREADS == 2 * kPadPartial, "two threads per pad-gradient channel");
 
-typedef __attribute__((address_space(3))) void lds_void;
-
 // Row r holds its 16-byte piece p at position p ^ (r & 15): the 16 rows a 16-lane read of one
 // piece touches cover all 64 banks.
 __device__ __forceinline__ int swz(int r) { return r & 15; }
-
-// wait until this wave's outstanding global loads (and the LDS writes of its direct loads) are done
-__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8)); }
 
 // the second part of LSE log2(e), lh = LSE kLog2eHi being the first (0 where that is infinite: a
 // query whose LSE the caller sets to +inf has P = 0)

@@ -83,6 +83,11 @@ struct WindowAddr {
     }
 };
 
+// ---- buffer loads that write LDS: the destination's type, and the wait for them
+typedef __attribute__((address_space(3))) void lds_void;
+// wait until this wave's outstanding global loads (and the LDS writes of its direct loads) are done
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8)); }
+
 // ---- rotary position embedding (RoPE) on bf16 channel pairs, for kernels without a
 //      per-window cos / sin table.  cos and sin of the angle pos * rev revolutions come from
 //      v_cos_f32 / v_sin_f32 after reducing it to [-1/2, 1/2] revolution.

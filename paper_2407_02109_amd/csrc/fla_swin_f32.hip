@@ -48,8 +48,6 @@ constexpr int kRopeTab = 32;           // window rows / columns covered by the R
 
 constexpr float kLn2Hi = 0.693147182f, kLn2Lo = -1.90465430e-9f;
 
-typedef __attribute__((address_space(3))) void lds_void;
-
 template <int D>
 struct Cfg {
     static constexpr int ROWP = D / 4;          // 16-byte pieces per row
@@ -72,9 +70,6 @@ template <int D>
 __device__ __forceinline__ int swz(int r) {
     return D == 32 ? (r >> 1) & 7 : r & 15;
 }
-
-// wait until this wave's outstanding global loads (and the LDS writes of its direct loads) are done
-__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8)); }
 
 template <int D, bool ROPE>
 __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(ROPE ? 2 : Cfg<D>::WAVES, ROPE ? 2 : Cfg<D>::WAVES)))

@@ -68,7 +68,8 @@ struct SwinArgs {
     int B, heads;
     int window, shift;
     int origin;                 // (window - shift) % window: virtual tokens in front of each axis
-    int nqb;                    // query blocks per window: ceil(max window size / kQueryBlock)
+    int nqb;                    // query blocks of the largest window: of kQueryBlock tokens as the host fills it;
+                                // launchers with other blocks (fp32, shared keys) set their own with div_nqb
     int pad_mode;               // 0 = mask virtual keys, 1 = pad token at row L
     int64_t L;                  // tokens per batch entry, all grids (the pad token's row)
     int64_t tok_stride;         // elements between consecutive tokens: heads * head_dim

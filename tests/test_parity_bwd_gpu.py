@@ -136,8 +136,8 @@ def test_lse_and_backward(shape, dtype, pm):
 @pytest.mark.parametrize("shape", WIDE, ids=lambda s: "x".join(map(str, s)))
 def test_backward_wide_windows(shape, dtype, pm):
     """Windows of more than 256 tokens: bf16 in 128-token blocks that each stream the whole
-    window's other side through LDS in 128-token chunks (the last ones partial); fp32 in the
-    three fp32 kernels."""
+    window's other side through LDS in 128-token chunks (the last ones partial); fp32 in
+    64-token blocks and chunks."""
     B, heads, H, W, k, s = shape
     _say("bwd wide %s %s pad_mode=%d" % (shape, dtype, pm))
     f32 = dtype == "f32"
