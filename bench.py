@@ -249,7 +249,7 @@ def summarize_cycle(prof_dir: str, command: str, out_dir: str = ""):
         return out
 
     def short(name):
-        m = re.search(r"(cycle_scan_\w+(?:<\d+>)?)", name)
+        m = re.search(r"(cycle_scan_\w+(?:<[^<>]*>)?)", name)
         return m.group(1) if m else None
 
     all_rows = sorted(rows("trace/**/*kernel_trace.csv"), key=lambda r: int(r["Start_Timestamp"]))

@@ -89,9 +89,9 @@ def test_roofline_follows_arithmetic_intensity():
 
 def test_cycle_summary_splits_cold_and_warm_calls_and_scales_counters(tmp_path):
     prof = tmp_path / "prof"
-    ch, ca, co = ("void fla::(anonymous namespace)::cycle_scan_chunks<32>(fla::CycleArgs)",
+    ch, ca, co = ("void fla::(anonymous namespace)::cycle_scan_chunks<32, 4, false>(fla::CycleArgs)",
                   "fla::(anonymous namespace)::cycle_scan_carries(fla::CycleArgs)",
-                  "void fla::(anonymous namespace)::cycle_scan_outputs<32>(fla::CycleArgs)")
+                  "void fla::(anonymous namespace)::cycle_scan_outputs<32, 1>(fla::CycleArgs)")
     flush = "void at::native::reduce_kernel<512, 1>(x)"
     # one cold call (after the flush: 30, 4, 40 us) and one warm call (20, 2, 30 us)
     trace = [[flush, "1", 0, 500], [ch, "3072", 1000, 31000], [ca, "96", 31000, 35000], [co, "3072", 35000, 75000],
@@ -109,9 +109,9 @@ def test_cycle_summary_splits_cold_and_warm_calls_and_scales_counters(tmp_path):
     out = tmp_path / "out"
     bench.summarize_cycle(str(prof), "rocprofv3 ... -- python3 bench.py", str(out))
     text = (out / "cycle_scan_cyclescan_img4096.md").read_text()
-    assert "| cycle_scan_chunks<32> | 1 | 30.00 | 1 | 20.00 | %.1f | - |" % (2000 * 1024 * 2 / 1e6) in text
+    assert "| cycle_scan_chunks<32, 4, false> | 1 | 30.00 | 1 | 20.00 | %.1f | - |" % (2000 * 1024 * 2 / 1e6) in text
     assert "| cycle_scan_carries | 1 | 4.00 | 1 | 2.00 | - | - |" in text
-    assert "| cycle_scan_outputs<32> | 1 | 40.00 | 1 | 30.00 | - | %.1f |" % (4000 * 1024 / 1e6) in text
+    assert "| cycle_scan_outputs<32, 1> | 1 | 40.00 | 1 | 30.00 | - | %.1f |" % (4000 * 1024 / 1e6) in text
     assert "| sum (one call) | | 74.00 | | 52.00 | | |" in text
     assert "Kernel source hash: %s" % bench.kernel_hash("cycle") in text
 
