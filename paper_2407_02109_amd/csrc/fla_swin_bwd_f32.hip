@@ -132,13 +132,15 @@ __device__ __forceinline__ floatx16 row_product(const Block& k, const float* row
 }
 
 // Rows 16 w .. 16 w + 15 of the chunk starting at window-local token `base` straight into the
-// swizzled LDS rows `dst`; rows past the window: zeros.
+// swizzled LDS rows `dst`; rows past the window: zeros (LAST: the window's last row).
+template <bool LAST = false>
 __device__ __forceinline__ void load_rows(const Block& k, __amdgpu_buffer_rsrc_t src, float* dst, int base) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int r = 16 * k.wave + 4 * i + (k.lane >> 4);
         const int p = (k.lane & 15) ^ swz(r);
-        const unsigned off = base + r < k.n ? k.addr(base + r) + 16 * p : kOutside;
+        const int t = base + r;
+        const unsigned off = LAST ? k.addr(min(t, k.n - 1)) + 16 * p : t < k.n ? k.addr(t) + 16 * p : kOutside;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (lds_void*)(dst + (16 * k.wave + 4 * i) * D), 16, off, 0, 0, 0);
     }
 }
@@ -223,7 +225,7 @@ __device__ __forceinline__ void key_role(const SwinBwdArgs& ba, const Block& k, 
     float lse;
     auto issue = [&](int c) {
         const int buf = c & 1, t = CH * c + pr;
-        load_rows(k, k.qr, smem + OFF_X + buf * BUF, CH * c);
+        load_rows<true>(k, k.qr, smem + OFF_X + buf * BUF, CH * c);
         load_rows(k, k.dor, smem + OFF_Y + buf * BUF, CH * c);
         const unsigned off = t < k.n ? k.addr(t) + 16 * qq : kOutside;
 #pragma unroll
@@ -253,7 +255,9 @@ __device__ __forceinline__ void key_role(const SwinBwdArgs& ba, const Block& k, 
         float* ND = smem + OFF_ND + buf * CH;
         float* PP = smem + OFF_PP + buf * CH;
         float* DSP = smem + OFF_DSP + buf * CH;
-        // ---- the wave's own rows of this chunk: LSE log2(e), D and the pad token's P and dS
+        // ---- the wave's own rows of this chunk: LSE log2(e), D and the pad token's P and dS.  Rows past
+        // the window get an LSE of +inf, which makes P zero: their Q is that of the window's last row, since
+        // the logit of a zero row and a key with an infinite component would be 0 * inf
         wait_loads();
         {
             float dd = 0.f, zp = 0.f, dp = 0.f;
@@ -269,6 +273,7 @@ __device__ __forceinline__ void key_role(const SwinBwdArgs& ba, const Block& k, 
             }
             dd += __shfl_xor(dd, 1);
             dd += __shfl_xor(dd, 2);
+            if (CH * c + pr >= k.n) lse = INFINITY;
             const float lh = lse * kLog2eHi;
             const float ll = lse_low(lse, lh);
             if (pad_here) {
@@ -307,11 +312,8 @@ __device__ __forceinline__ void key_role(const SwinBwdArgs& ba, const Block& k, 
                 }
             pad_sum += (s4[0] + s4[1]) + (s4[2] + s4[3]);
         }
-        const int nv = k.n - (CH * c + TL * k.sh);   // queries of the wave's tile
-        if (!work || nv <= 0) continue;
-        // ---- the streamed tile (register r: query 8 (r / 4) + 4 h + r % 4) against the wave's keys;
-        // rows past the window are zero, and P is cleared there: a key with an infinite component
-        // makes their logit 0 * inf
+        if (!work || CH * c + TL * k.sh >= k.n) continue;
+        // ---- the streamed tile (register r: query 8 (r / 4) + 4 h + r % 4) against the wave's keys
         const floatx16 s = row_product(k, Qs, kreg, floatx16{});
         floatx16 dp;
 #pragma unroll
@@ -330,8 +332,7 @@ __device__ __forceinline__ void key_role(const SwinBwdArgs& ba, const Block& k, 
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int r = 4 * i + j;
-                const float e = __builtin_amdgcn_exp2f((s[r] - hv[j]) - lv[j]);
-                const float p = 8 * i + 4 * k.h + j < nv ? e : 0.f;
+                const float p = __builtin_amdgcn_exp2f((s[r] - hv[j]) - lv[j]);
                 const float ds = p * dp[r];
 #pragma unroll
                 for (int db = 0; db < 2; ++db) {
