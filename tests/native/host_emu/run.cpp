@@ -238,8 +238,7 @@ static int run_bf16_train(int argc, char** argv) {
 }
 
 // Launch failure: every entry point must return FLA_ERR_LAUNCH and leave its outputs as they
-// were: the emulated runtime is told to fail every launch (the bf16 backward launchers of this
-// build, which does not contain those kernels, fail anyway).
+// were: the emulated runtime is told to fail every launch.
 static int run_launchfail() {
     const int B = 1, heads = 2, H = 20, W = 13, k = 8, s = 3;
     const size_t L = (size_t)H * W, rows = L + 1, tok = (size_t)heads * 64;
